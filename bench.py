@@ -114,7 +114,7 @@ def mangled_name(short):
     if not m:
         return None
     name, args = m.group(1), [a.strip() for a in m.group(2).split(",")]
-    enc = "".join(f"Lb{1 if a == 'true' else 0}E" if a in ("true", "false") else f"Li{a}E"
+    enc = "".join(f"Lb{1 if a == 'true' else 0}E" if a in ("true", "false") else f"Li{a.replace('-', 'n')}E"
                   for a in args)
     params = {"stream_kernel": "NS_10StreamArgsE", "tail_kernel": "NS_8TailArgsE",
               "combine_kernel": "PK15HIP_vector_typeIiLj4EElPdliPflPKff"}.get(name)

@@ -130,6 +130,12 @@ typedef enum {
  *                                       variant, every pass (default: 32, 8
  *                                       for dR from b = 128; bitwise the
  *                                       same);
+ *   KBFOLLOW_SCALAR_LANES=1             one float per lane wherever b is not
+ *                                       a multiple of 4 (default: below b = 5)
+ *   KBFOLLOW_PREFILL=0|1                rows without triples written one by
+ *                                       one / by a sweep over the whole output
+ *                                       before the stream kernel (default: by
+ *                                       their number and width)
  *   KBFOLLOW_STREAM_STAMPS=0            phase timing of the stream kernels by
  *                                       event records instead of their
  *                                       dispatch timestamps.

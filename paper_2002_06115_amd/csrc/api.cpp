@@ -81,6 +81,8 @@ struct kb_t {
   bool weighted = false;
   bool plain_loads = false;  // force plain loads instead of raw buffer loads (testing)
   bool b_in_lds = true;      // stage small B tables in LDS (off: B rows in registers)
+  int prefill = -1;          // empty rows by a sweep over the whole output: -1 by prefill_rows, 0 never, 1 always
+  bool scalar_lanes = false; // one float per lane wherever b % 4 != 0 (testing)
   bool stream_stamps = true; // time stream kernels by their dispatch timestamps (off: event records)
   int max_lpt = 0;           // widest lane group of the register variant; 0: per pass (lane_cap)
   // The backward's dR pass on a stream of the KB's own, concurrent with the
@@ -246,6 +248,28 @@ int lane_cap(const kb_t *kb, int ph_base, int32_t b) {
   return (ph_base == KB_PH_DR_STREAM && b >= 128) ? 8 : 32;
 }
 
+// Whether a pass writes its empty rows by filling the whole output in one
+// contiguous sweep before the stream kernel (which overwrites the other rows),
+// instead of row by row in the tail launch.  Rows of whole 64-byte lines
+// scatter well (4.6 TB/s at b = 32), others do not: on a KB of 12.9 M entities,
+// 7.77 M of them empty, the row-by-row fill took 35 to 60 ps a row at widths
+// that are a multiple of 4 but not of 16, and 98 to 190 at ragged ones (five
+// narrow stores a row), against 0.65 ps per float of the whole output for the
+// sweep (forward at b = 10: 1780 -> 888 us, b = 8: 926 -> 740, b = 24: 1350 ->
+// 1130, b = 1: 588 -> 508; at b = 32 the sweep would lose, 885 -> 936).  The
+// residual hop's fill also reads a row for each (b = 10: 2020 -> 1352 us, b =
+// 32: 1207 -> 1315, not taken).  The sweep is one more launch.
+bool prefill_rows(const kb_t *kb, const DevLayout &D, int32_t b, bool res) {
+  if (D.n_empty == 0 || D.rows > (int64_t(1) << 33) / b) return false;
+  if (kb->prefill >= 0) return kb->prefill > 0;
+  const double w = (double)b;
+  double row = b % 16 == 0 ? 5.0 + 0.75 * w : b % 4 == 0 ? 35.0 + 0.9 * w
+               : b >= kMinRagged ? 120.0 + 0.7 * w : 12.0 * w;  // ps
+  if (res) row += 15.0 + 0.3 * w;
+  const double sweep = (res ? 1.3 : 0.65) * w;
+  return (double)D.n_empty * row > (double)D.rows * sweep + (res ? 2e6 : 6.5e6);
+}
+
 // Runs one pass: the stream kernel, the first combine level together with
 // the empty rows, the further combine levels.  With Z non-null (one row per
 // output row; A itself for the residual hop, out itself to add in place)
@@ -255,6 +279,12 @@ kb_status run_pass(const kb_t *kb, const DevLayout &D, int ph_base, const float 
                    void *ws, const float *Z, float gamma, hipStream_t s) {
   double *slots = static_cast<double *>(ws);
   const float *res = Z;
+  const bool prefill = Z != out && prefill_rows(kb, D, b, Z != nullptr);
+  if (prefill) {
+    PhaseScope scope(kb, ph_base + 1, s);
+    hipError_t e = launch_fill(out, D.rows * (int64_t)b, res, gamma, s);
+    if (e != hipSuccess) return hip_fail(e, "fill kernel launch");
+  }
   if (D.n > 0) {
     // Timed by the kernel's own timestamps: no event packets between this
     // launch and the next, which would hold back a concurrent pass.
@@ -266,6 +296,7 @@ kb_status run_pass(const kb_t *kb, const DevLayout &D, int ph_base, const float 
     StreamOptions o;
     o.plain_loads = kb->plain_loads;
     o.b_in_lds = kb->b_in_lds;
+    o.scalar_lanes = kb->scalar_lanes;
     o.n_cu = kb->n_cu;
     o.max_lpt = lane_cap(kb, ph_base, b);
     hipError_t e = launch_stream(a, o, s, scope.launch_start(), scope.launch_stop());
@@ -275,8 +306,8 @@ kb_status run_pass(const kb_t *kb, const DevLayout &D, int ph_base, const float 
     // The first combine level and the empty rows share one launch.
     PhaseScope scope(kb, ph_base + 1, s);
     const int64_t n0 = D.level_begin.size() > 1 ? D.level_begin[1] - D.level_begin[0] : 0;
-    TailArgs t{D.ctasks, n0, slots, D.n_slots, D.empty, D.n_empty_pieces, b, out, D.rows, res,
-               gamma, 0};
+    TailArgs t{D.ctasks, n0, slots, D.n_slots, D.empty, prefill ? 0 : D.n_empty_pieces, b, out,
+               D.rows, res, gamma, 0};
     hipError_t e = launch_tail(t, s);
     if (e != hipSuccess) return hip_fail(e, "combine and empty-row kernel launch");
   }
@@ -391,6 +422,8 @@ kb_status kb_create(int64_t n_entities, int64_t n_relations, int64_t n_triples,
     if (kb->n_cu <= 0) kb->n_cu = 1;
     kb->plain_loads = env_int("KBFOLLOW_PLAIN_LOADS", 0) != 0;
     kb->b_in_lds = env_int("KBFOLLOW_B_IN_LDS", 1) != 0;
+    kb->scalar_lanes = env_int("KBFOLLOW_SCALAR_LANES", 0) != 0;
+    kb->prefill = env_int("KBFOLLOW_PREFILL", -1);
     kb->stream_stamps = env_int("KBFOLLOW_STREAM_STAMPS", 1) != 0;
     kb->max_lpt = env_int("KBFOLLOW_MAX_LPT", 0);
     // dR concurrent with dX from 2^20 triples on, at b <= 32 (measured on the
@@ -758,6 +791,7 @@ kb_status kb_phase_kernel(const kb_t *kb, int32_t b, int32_t phase, int32_t resi
       StreamOptions o;
       o.plain_loads = kb->plain_loads;
       o.b_in_lds = kb->b_in_lds;
+      o.scalar_lanes = kb->scalar_lanes;
       o.n_cu = kb->n_cu;
       o.max_lpt = lane_cap(kb, pass * 3, b);
       out = describe_stream(a, o);

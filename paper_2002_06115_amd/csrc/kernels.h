@@ -11,14 +11,18 @@ namespace kbf {
 
 // How the columns of a b-wide row are spread over the lanes of a lane group.
 struct ColumnTiling {
-  int vec;       // floats per lane per access: 4 (b % 4 == 0) or 1
+  int vec;       // floats per lane per access: 4, or 1 for b < 5 not a multiple of 4
+  bool ragged;   // 4 floats per lane although b % 4 != 0: the last lane of a row takes its last 4
   int lpt;       // lanes per group (power of two, <= 32): one group walks one chunk
   int width;     // columns one group covers, lpt * vec
   int n_slices;  // ceil(b / width): grid y dimension
 };
+// Narrowest row that is read 4 floats per lane where b % 4 != 0.
+constexpr int kMinRagged = 5;
 ColumnTiling column_tiling(int32_t b);
-// The same with lane groups of at most max_lpt lanes (a power of two <= 32).
-ColumnTiling column_tiling_max(int32_t b, int max_lpt);
+// The same with lane groups of at most max_lpt lanes (a power of two <= 32);
+// scalar: one float per lane wherever b % 4 != 0.
+ColumnTiling column_tiling_max(int32_t b, int max_lpt, bool scalar = false);
 
 // Chunk lengths must be multiples of this (the kernel's step, kUnroll entries).
 constexpr int32_t kChunkQuantum = 8;
@@ -78,6 +82,9 @@ struct StreamOptions {
   // rows in registers, the variant used for larger tables.
   bool b_in_lds = true;
   int n_cu = 1;  // compute units of the device, for the LDS variant's grid
+  // One float per lane wherever b % 4 != 0 (the layout of b < 5), so that the
+  // two layouts can be compared.
+  bool scalar_lanes = false;
   int max_lpt = 32;  // widest lane group of the register variant (narrower: more column slices)
 };
 // With start / stop events the kernel is launched with hipExtLaunchKernel,
@@ -116,6 +123,9 @@ struct TailArgs {
   int64_t combine_blocks;
 };
 hipError_t launch_tail(const TailArgs &a, hipStream_t s);
+// +0.0, or gamma * res[i] when res is not null, to n floats (at most 2^33)
+// from p on, in one contiguous sweep; res must not overlap p.
+hipError_t launch_fill(float *p, int64_t n, const float *res, float gamma, hipStream_t s);
 std::string describe_tail(const TailArgs &a);
 std::string describe_combine(int32_t b);
 

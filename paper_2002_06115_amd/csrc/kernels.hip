@@ -125,20 +125,25 @@ __device__ __forceinline__ int group_bcast(int v) {
   }
 }
 
+typedef float native_float4 __attribute__((ext_vector_type(4)));
+// The same at any float's / double's address: rows whose width is not a
+// multiple of 4 floats start anywhere, and gfx950's 16-byte loads and stores
+// take any 4-byte boundary.
+typedef float float4_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef double double2_any __attribute__((ext_vector_type(2), aligned(8)));
+
 template <int VEC>
 __device__ __forceinline__ void load_row(const float *__restrict__ p, float (&v)[VEC]) {
   if constexpr (VEC == 4) {
-    const float4 t = *reinterpret_cast<const float4 *>(p);
-    v[0] = t.x;
-    v[1] = t.y;
-    v[2] = t.z;
-    v[3] = t.w;
+    const float4_any t = *reinterpret_cast<const float4_any *>(p);
+    v[0] = t[0];
+    v[1] = t[1];
+    v[2] = t[2];
+    v[3] = t[3];
   } else {
     v[0] = *p;
   }
 }
-
-typedef float native_float4 __attribute__((ext_vector_type(4)));
 
 // Record index that no table of this library reaches.
 constexpr uint32_t kNoRecord = 0xFFFFFFFFu;
@@ -187,6 +192,30 @@ __device__ __forceinline__ void lds_row(const float *p, float (&v)[VEC]) {
     v[0] = *p;
   }
 }
+// The columns a lane of VEC floats works on, c0 being where its place in the
+// row begins (c0 < b).  Rows of b floats, b not a multiple of 4, end in a lane
+// whose 4 columns would pass the row's end: it takes the last 4 of the row
+// instead (so that every 16-byte load stays inside its row; b >= 5 there).
+// The first `skip` of them belong to the lane before it: both compute them,
+// the same sums in the same order, bit for bit.  In the stream kernel both
+// store them too (one 16-byte store per lane; the same bits from both), unless
+// the pass adds rows of Z, which may be the output: there a column is only
+// stored by the lane it belongs to, so that no Z is read after its own row was
+// written.
+struct LaneCols {
+  int c;     // first column read
+  int skip;  // columns of these that belong to the lane before
+};
+template <bool RAGGED>
+__device__ __forceinline__ LaneCols lane_cols(int c0, int b) {
+  if constexpr (RAGGED) {
+    const int c = min(c0, b - 4);
+    return {c, c0 - c};
+  } else {
+    return {c0, 0};
+  }
+}
+
 template <int VEC>
 __device__ __forceinline__ void lds_store(float *p, const float (&v)[VEC]) {
   if constexpr (VEC == 4)
@@ -201,21 +230,34 @@ template <int VEC>
 __device__ __forceinline__ void store_row(float *__restrict__ p, const double (&acc)[VEC]) {
   if constexpr (VEC == 4) {
     const native_float4 v = {(float)acc[0], (float)acc[1], (float)acc[2], (float)acc[3]};
-    __builtin_nontemporal_store(v, reinterpret_cast<native_float4 *>(p));
+    __builtin_nontemporal_store(v, reinterpret_cast<float4_any *>(p));
   } else {
     __builtin_nontemporal_store((float)acc[0], p);
+  }
+}
+
+// store_row / store_slot without the first `skip` columns (LaneCols).
+template <int VEC>
+__device__ __forceinline__ void store_row_from(float *__restrict__ p, const double (&acc)[VEC],
+                                               int skip) {
+  if (VEC == 1 || skip == 0) {
+    store_row<VEC>(p, acc);
+  } else {
+#pragma unroll
+    for (int v = 1; v < VEC; ++v)
+      if (v >= skip) __builtin_nontemporal_store((float)acc[v], p + v);
   }
 }
 
 template <int VEC>
 __device__ __forceinline__ void load_slot(const double *__restrict__ p, double (&v)[VEC]) {
   if constexpr (VEC == 4) {
-    const double2 t0 = reinterpret_cast<const double2 *>(p)[0];
-    const double2 t1 = reinterpret_cast<const double2 *>(p)[1];
-    v[0] = t0.x;
-    v[1] = t0.y;
-    v[2] = t1.x;
-    v[3] = t1.y;
+    const double2_any t0 = reinterpret_cast<const double2_any *>(p)[0];
+    const double2_any t1 = reinterpret_cast<const double2_any *>(p)[1];
+    v[0] = t0[0];
+    v[1] = t0[1];
+    v[2] = t1[0];
+    v[3] = t1[1];
   } else {
     v[0] = *p;
   }
@@ -224,10 +266,22 @@ __device__ __forceinline__ void load_slot(const double *__restrict__ p, double (
 template <int VEC>
 __device__ __forceinline__ void store_slot(double *__restrict__ p, const double (&acc)[VEC]) {
   if constexpr (VEC == 4) {
-    reinterpret_cast<double2 *>(p)[0] = make_double2(acc[0], acc[1]);
-    reinterpret_cast<double2 *>(p)[1] = make_double2(acc[2], acc[3]);
+    reinterpret_cast<double2_any *>(p)[0] = double2_any{acc[0], acc[1]};
+    reinterpret_cast<double2_any *>(p)[1] = double2_any{acc[2], acc[3]};
   } else {
     *p = acc[0];
+  }
+}
+
+template <int VEC>
+__device__ __forceinline__ void store_slot_from(double *__restrict__ p, const double (&acc)[VEC],
+                                                int skip) {
+  if (VEC == 1 || skip == 0) {
+    store_slot<VEC>(p, acc);
+  } else {
+#pragma unroll
+    for (int v = 1; v < VEC; ++v)
+      if (v >= skip) p[v] = acc[v];
   }
 }
 
@@ -302,15 +356,21 @@ __device__ __forceinline__ void store_row_buffer(__amdgpu_buffer_rsrc_t rsrc, ui
 // The same cap on the soft-KB variants or on narrower lane groups spilled
 // inside the loop and ran slower, so they keep the compiler's own
 // allocation.
-template <int VEC, int LPT, bool WEIGHTED, bool RES, bool LDSB>
+constexpr int kRaggedLane = -4;
+template <int LANE, int LPT, bool WEIGHTED, bool RES, bool LDSB>
 constexpr int stream_min_waves() {
-  return (LDSB && !WEIGHTED && VEC == 4 && (RES ? LPT >= 8 : LPT == 8)) ? 6 : 1;
+  return (LDSB && !WEIGHTED && LANE != 1 && (RES ? LPT >= 8 : LPT == 8)) ? 6 : 1;
 }
 
-template <int VEC, int LPT, bool BUF, bool WEIGHTED, bool RES, bool LDSB>
+//
+// LANE: floats per lane, 1 or 4, or kRaggedLane: 4 where b >= 5 is not a
+// multiple of 4 (see LaneCols).
+template <int LANE, int LPT, bool BUF, bool WEIGHTED, bool RES, bool LDSB>
 __global__ __launch_bounds__((LDSB ? kBlockLdsBig : kBlock),
-                             (stream_min_waves<VEC, LPT, WEIGHTED, RES, LDSB>())) void
+                             (stream_min_waves<LANE, LPT, WEIGHTED, RES, LDSB>())) void
 stream_kernel(StreamArgs a) {
+  constexpr bool RAGGED = LANE == kRaggedLane;
+  constexpr int VEC = RAGGED ? 4 : LANE;
   static_assert(BUF || !LDSB, "the LDS copy of B goes with raw buffer loads");
   const int BLK = LDSB ? (int)blockDim.x : kBlock;  // kBlockLds or kBlockLdsBig
   const int GPB = BLK / LPT;
@@ -318,8 +378,9 @@ stream_kernel(StreamArgs a) {
   extern __shared__ float b_lds[];  // [B_rows][W] with LDSB
   const int lane = threadIdx.x % LPT;
   const int grp = threadIdx.x / LPT;
-  const int c = blockIdx.y * (LPT * VEC) + lane * VEC;
-  const bool active = c < a.b;
+  const int c0 = blockIdx.y * (LPT * VEC) + lane * VEC;
+  const bool active = c0 < a.b;
+  const int c = lane_cols<RAGGED>(c0, a.b).c, skip = lane_cols<RAGGED>(c0, a.b).skip;
   const size_t bb = (size_t)a.b;
   // Lanes past b read column 0 and store nothing.
   const int cl = active ? c : 0;
@@ -371,7 +432,8 @@ stream_kernel(StreamArgs a) {
       const int j = (int)(i % W);
       float v[VEC];
       if (col0 + j < a.b) {
-        load_row<VEC>(a.B + (size_t)KBF_CHECKED(r, a.B_rows) * bb + col0 + j, v);
+        const int cj = lane_cols<RAGGED>(col0 + j, a.b).c;
+        load_row<VEC>(a.B + (size_t)KBF_CHECKED(r, a.B_rows) * bb + cj, v);
       } else {
 #pragma unroll
         for (int q = 0; q < VEC; ++q) v[q] = 0.0f;
@@ -551,7 +613,13 @@ stream_kernel(StreamArgs a) {
 #pragma unroll
           for (int v = 0; v < VEC; ++v)
             y[v] = (RES && f >= 0) ? acc[v] + (double)a.gamma * (double)xa[u][v] : acc[v];
-          if (f >= 0) {
+          if constexpr (RAGGED && RES) {
+            if (f >= 0)
+              store_row_from<VEC>(a.out + (size_t)KBF_CHECKED(f, a.out_rows) * bb + c, y, skip);
+            else
+              store_slot_from<VEC>(a.slots + (size_t)KBF_CHECKED(-(f + 1), a.n_slots) * bb + c, y,
+                                   skip);
+          } else if (f >= 0) {
             if constexpr (BUF)
               store_row_buffer<VEC>(
                   orsrc, (uint32_t)KBF_CHECKED(f, a.out_rows) * row_bytes + col_bytes, y);
@@ -590,7 +658,7 @@ stream_kernel(StreamArgs a) {
 
 // Adds slots [first, first + n) in increasing order; writes the float row or
 // a next-level slot.  `block` of `n_blocks` blocks share the tasks.
-template <int VEC, int LPT>
+template <int VEC, int LPT, bool RAGGED>
 __device__ __forceinline__ void combine_tasks(const int4 *__restrict__ tasks, int64_t n_tasks,
                                               double *__restrict__ slots, int64_t n_slots,
                                               int32_t b, float *out, int64_t out_rows,
@@ -600,8 +668,9 @@ __device__ __forceinline__ void combine_tasks(const int4 *__restrict__ tasks, in
   constexpr int GPB = kBlock / LPT;
   const int lane = threadIdx.x % LPT;
   const int grp = threadIdx.x / LPT;
-  const int c = blockIdx.y * W + lane * VEC;
-  if (c >= b) return;  // no barrier below
+  const int c0 = blockIdx.y * W + lane * VEC;
+  if (c0 >= b) return;  // no barrier below
+  const int c = lane_cols<RAGGED>(c0, b).c, skip = lane_cols<RAGGED>(c0, b).skip;
   const size_t bb = (size_t)b;
   const int64_t stride = n_blocks * GPB;
   for (int64_t t = block * GPB + grp; t < n_tasks; t += stride) {
@@ -631,9 +700,10 @@ __device__ __forceinline__ void combine_tasks(const int4 *__restrict__ tasks, in
 #pragma unroll
         for (int v = 0; v < VEC; ++v) acc[v] += (double)gamma * (double)r[v];
       }
-      store_row<VEC>(out + row * bb + c, acc);
+      store_row_from<VEC>(out + row * bb + c, acc, skip);
     } else {
-      store_slot<VEC>(slots + (size_t)KBF_CHECKED(-(int64_t)tk.z - 1, n_slots) * bb + c, acc);
+      store_slot_from<VEC>(slots + (size_t)KBF_CHECKED(-(int64_t)tk.z - 1, n_slots) * bb + c, acc,
+                           skip);
     }
   }
 }
@@ -645,7 +715,7 @@ __device__ __forceinline__ void combine_tasks(const int4 *__restrict__ tasks, in
 // stands in front of the stores of 64 pieces per wave.  Otherwise one piece
 // per group: the residual hop's rows each need a load of X of their own.
 // `block` of `n_blocks` blocks share the pieces.
-template <int VEC, int LPT, bool PACKED>
+template <int VEC, int LPT, bool PACKED, bool RAGGED>
 __device__ __forceinline__ void zero_pieces(const int2 *__restrict__ pieces, int64_t n_pieces,
                                             int32_t b, float *out, int64_t out_rows,
                                             const float *res, float gamma, int64_t block,
@@ -654,7 +724,9 @@ __device__ __forceinline__ void zero_pieces(const int2 *__restrict__ pieces, int
   constexpr int GPB = kBlock / LPT;
   const int lane = threadIdx.x % LPT;
   const int grp = threadIdx.x / LPT;
-  const int c = blockIdx.y * W + lane * VEC;
+  const int c0 = blockIdx.y * W + lane * VEC;
+  const bool active = c0 < b;
+  const int c = lane_cols<RAGGED>(c0, b).c, skip = lane_cols<RAGGED>(c0, b).skip;
   const size_t bb = (size_t)b;
   if constexpr (PACKED) {
     const int64_t stride = n_blocks * kBlock;
@@ -666,13 +738,14 @@ __device__ __forceinline__ void zero_pieces(const int2 *__restrict__ pieces, int
       for (int j = 0; j < LPT; ++j) {
         const int first = __shfl(mine.x, base + j);
         const int count = __shfl(mine.y, base + j);
-        if (c >= b) continue;  // after the shuffles, which every lane joins
+        if (!active) continue;  // after the shuffles, which every lane joins
         for (int i = 0; i < count; ++i) {
           const double z[VEC] = {};
           // Non-temporal, like every output row: plain stores would leave
           // the rows dirty in the caches, to be written back during the next
           // pass.
-          store_row<VEC>(out + (size_t)KBF_CHECKED((int64_t)first + i, out_rows) * bb + c, z);
+          store_row_from<VEC>(out + (size_t)KBF_CHECKED((int64_t)first + i, out_rows) * bb + c, z,
+                              skip);
         }
       }
     }
@@ -683,7 +756,7 @@ __device__ __forceinline__ void zero_pieces(const int2 *__restrict__ pieces, int
     // batch's row loads are issued before its stores, so the mostly one- or
     // two-row pieces of a Zipf KB still keep many loads in flight.  (res may
     // be out itself: each row is read and then written by the same lane.)
-    if (c >= b) return;  // no barrier or shuffle below
+    if (!active) return;  // no barrier or shuffle below
     const int64_t stride = n_blocks * GPB * kFillPieces;
     for (int64_t t0 = (block * GPB + grp) * kFillPieces; t0 < n_pieces; t0 += stride) {
       int first[kFillPieces], start[kFillPieces], end[kFillPieces];
@@ -717,10 +790,31 @@ __device__ __forceinline__ void zero_pieces(const int2 *__restrict__ pieces, int
           double y[VEC];
 #pragma unroll
           for (int v = 0; v < VEC; ++v) y[v] = 0.0 + (double)gamma * (double)r[u][v];
-          store_row<VEC>(out + (size_t)KBF_CHECKED((int64_t)row[u], out_rows) * bb + c, y);
+          store_row_from<VEC>(out + (size_t)KBF_CHECKED((int64_t)row[u], out_rows) * bb + c, y,
+                              skip);
         }
       }
     }
+  }
+}
+
+// +0.0, or gamma * res[i], to n floats from p on: 16 bytes per thread.  (A
+// grid of as many workgroups as the chip holds, walking the range, wrote
+// 1.66 GB of zeros at 4.6 TB/s; one store per thread writes them at 6.6.
+// Plain stores reach 6.9, but the lines they leave in the caches made the
+// stream kernel behind them 6 % slower.)
+template <bool RES>
+__global__ __launch_bounds__(kBlock) void fill_kernel(float *__restrict__ p, int64_t n,
+                                                      const float *__restrict__ res, float gamma) {
+  const int64_t i = ((int64_t)blockIdx.x * kBlock + threadIdx.x) * 4;
+  auto value = [&](float r) { return RES ? 0.0 + (double)gamma * (double)r : 0.0; };
+  if (i + 4 <= n) {
+    float r[4] = {};
+    if constexpr (RES) load_row<4>(res + i, r);
+    const double y[4] = {value(r[0]), value(r[1]), value(r[2]), value(r[3])};
+    store_row<4>(p + i, y);
+  } else {
+    for (int64_t k = i; k < n; ++k) p[k] = (float)value(RES ? res[k] : 0.0f);
   }
 }
 
@@ -732,8 +826,23 @@ __global__ __launch_bounds__(kBlock) void combine_kernel(const int4 *__restrict_
                                                          int64_t n_slots, int32_t b,
                                                          float *out, int64_t out_rows,
                                                          const float *res, float gamma) {
-  combine_tasks<VEC, LPT>(tasks, n_tasks, slots, n_slots, b, out, out_rows, res, gamma,
-                          blockIdx.x, gridDim.x);
+  if (VEC == 4 && b % 4 != 0)
+    combine_tasks<VEC, LPT, VEC == 4>(tasks, n_tasks, slots, n_slots, b, out, out_rows, res, gamma,
+                                      blockIdx.x, gridDim.x);
+  else
+    combine_tasks<VEC, LPT, false>(tasks, n_tasks, slots, n_slots, b, out, out_rows, res, gamma,
+                                   blockIdx.x, gridDim.x);
+}
+
+template <int VEC, int LPT, bool PACKED, bool RAGGED>
+__device__ __forceinline__ void tail_blocks(const TailArgs &a) {
+  if ((int64_t)blockIdx.x < a.combine_blocks)
+    combine_tasks<VEC, LPT, RAGGED>(a.tasks, a.n_tasks, a.slots, a.n_slots, a.b, a.out, a.out_rows,
+                                    a.res, a.gamma, blockIdx.x, a.combine_blocks);
+  else
+    zero_pieces<VEC, LPT, PACKED, RAGGED>(a.pieces, a.n_pieces, a.b, a.out, a.out_rows, a.res,
+                                          a.gamma, (int64_t)blockIdx.x - a.combine_blocks,
+                                          (int64_t)gridDim.x - a.combine_blocks);
 }
 
 // The first combine level and the empty rows in one launch: blocks
@@ -742,39 +851,45 @@ __global__ __launch_bounds__(kBlock) void combine_kernel(const int4 *__restrict_
 // overlap with the fill's stores instead of forming a launch of their own.
 template <int VEC, int LPT, bool PACKED>
 __global__ __launch_bounds__(kBlock) void tail_kernel(TailArgs a) {
-  if ((int64_t)blockIdx.x < a.combine_blocks)
-    combine_tasks<VEC, LPT>(a.tasks, a.n_tasks, a.slots, a.n_slots, a.b, a.out, a.out_rows,
-                            a.res, a.gamma, blockIdx.x, a.combine_blocks);
+  if (VEC == 4 && a.b % 4 != 0)
+    tail_blocks<VEC, LPT, PACKED, VEC == 4>(a);
   else
-    zero_pieces<VEC, LPT, PACKED>(a.pieces, a.n_pieces, a.b, a.out, a.out_rows, a.res, a.gamma,
-                                  (int64_t)blockIdx.x - a.combine_blocks,
-                                  (int64_t)gridDim.x - a.combine_blocks);
+    tail_blocks<VEC, LPT, PACKED, false>(a);
 }
 
-template <int VEC, bool BUF, bool WT, bool RES, bool LDSB>
+template <int LANE, bool BUF, bool WT, bool RES, bool LDSB>
 const void *stream_fn(int lpt) {
   switch (lpt) {
-    case 1: return reinterpret_cast<const void *>(&stream_kernel<VEC, 1, BUF, WT, RES, LDSB>);
-    case 2: return reinterpret_cast<const void *>(&stream_kernel<VEC, 2, BUF, WT, RES, LDSB>);
-    case 4: return reinterpret_cast<const void *>(&stream_kernel<VEC, 4, BUF, WT, RES, LDSB>);
-    case 8: return reinterpret_cast<const void *>(&stream_kernel<VEC, 8, BUF, WT, RES, LDSB>);
-    case 16: return reinterpret_cast<const void *>(&stream_kernel<VEC, 16, BUF, WT, RES, LDSB>);
-    case 32: return reinterpret_cast<const void *>(&stream_kernel<VEC, 32, BUF, WT, RES, LDSB>);
+    case 1:
+      if constexpr (LANE == kRaggedLane)
+        return nullptr;  // at least two lanes
+      else
+        return reinterpret_cast<const void *>(&stream_kernel<LANE, 1, BUF, WT, RES, LDSB>);
+    case 2: return reinterpret_cast<const void *>(&stream_kernel<LANE, 2, BUF, WT, RES, LDSB>);
+    case 4: return reinterpret_cast<const void *>(&stream_kernel<LANE, 4, BUF, WT, RES, LDSB>);
+    case 8: return reinterpret_cast<const void *>(&stream_kernel<LANE, 8, BUF, WT, RES, LDSB>);
+    case 16: return reinterpret_cast<const void *>(&stream_kernel<LANE, 16, BUF, WT, RES, LDSB>);
+    case 32: return reinterpret_cast<const void *>(&stream_kernel<LANE, 32, BUF, WT, RES, LDSB>);
   }
   return nullptr;
 }
 
-template <int VEC, bool BUF, bool LDSB>
+template <int LANE, bool BUF, bool LDSB>
 const void *stream_fn_sel(int lpt, bool wt, bool res) {
   if (wt)
-    return res ? stream_fn<VEC, BUF, true, true, LDSB>(lpt)
-               : stream_fn<VEC, BUF, true, false, LDSB>(lpt);
-  return res ? stream_fn<VEC, BUF, false, true, LDSB>(lpt)
-             : stream_fn<VEC, BUF, false, false, LDSB>(lpt);
+    return res ? stream_fn<LANE, BUF, true, true, LDSB>(lpt)
+               : stream_fn<LANE, BUF, true, false, LDSB>(lpt);
+  return res ? stream_fn<LANE, BUF, false, true, LDSB>(lpt)
+             : stream_fn<LANE, BUF, false, false, LDSB>(lpt);
 }
 
 // Plain loads never take the LDS copy of B.
 const void *stream_fn_for(const ColumnTiling &t, bool buf, bool lds, bool wt, bool res) {
+  if (t.ragged) {
+    if (!buf) return stream_fn_sel<kRaggedLane, false, false>(t.lpt, wt, res);
+    return lds ? stream_fn_sel<kRaggedLane, true, true>(t.lpt, wt, res)
+               : stream_fn_sel<kRaggedLane, true, false>(t.lpt, wt, res);
+  }
   if (t.vec == 4) {
     if (!buf) return stream_fn_sel<4, false, false>(t.lpt, wt, res);
     return lds ? stream_fn_sel<4, true, true>(t.lpt, wt, res)
@@ -843,9 +958,16 @@ int64_t blocks_for(int64_t items, int per_block, int max_blocks) {
 
 ColumnTiling column_tiling(int32_t b) { return column_tiling_max(b, kMaxLpt); }
 
-ColumnTiling column_tiling_max(int32_t b, int max_lpt) {
+ColumnTiling column_tiling_max(int32_t b, int max_lpt, bool scalar) {
   ColumnTiling t;
-  t.vec = (b % 4 == 0) ? 4 : 1;
+  // Rows whose width is not a multiple of 4 are read 4 floats per lane too,
+  // from 5 floats on (see LaneCols): one float per lane needs up to four
+  // times the gather instructions, which are what the stream kernels' time
+  // follows (forward stream kernel at b = 10 on a KB of 12.9 M entities and
+  // 43.7 M triples 2680 -> 780 us, at b = 93 on one of 43 k entities and 190 k
+  // triples 47 -> 19 us).
+  t.ragged = b % 4 != 0 && b >= kMinRagged && !scalar;
+  t.vec = (b % 4 == 0 || t.ragged) ? 4 : 1;
   const int lanes = (b + t.vec - 1) / t.vec;
   // Lane groups of at most kMaxLpt lanes: wider rows are cut into column
   // slices of 128 columns (4 floats per lane), each a pass of its own over the
@@ -870,11 +992,11 @@ struct StreamChoice {
   int block = 0;
   size_t lds_bytes = 0;
   int vec = 0, lpt = 0;
-  bool buf = false, wt = false, res = false, ldsb = false;
+  bool ragged = false, buf = false, wt = false, res = false, ldsb = false;
 };
 
 hipError_t choose_stream(const StreamArgs &a, const StreamOptions &o, StreamChoice *c) {
-  const ColumnTiling t = column_tiling(a.b);
+  const ColumnTiling t = column_tiling_max(a.b, kMaxLpt, o.scalar_lanes);
   if (a.chunk % kChunkQuantum != 0 || a.n % a.chunk != 0) return hipErrorInvalidValue;
   // Raw-buffer offsets are 32-bit and a structured buffer's record stride is
   // at most kMaxStride bytes: tables of 4 GB or more, or rows of more than
@@ -898,13 +1020,15 @@ hipError_t choose_stream(const StreamArgs &a, const StreamOptions &o, StreamChoi
   }
   const int nl = a.n_lists;
   // The register variant's lane groups: at most o.max_lpt lanes wide.
-  const ColumnTiling tr = column_tiling_max(a.b, std::max(1, std::min(o.max_lpt, kMaxLpt)));
+  const ColumnTiling tr =
+      column_tiling_max(a.b, std::max(1, std::min(o.max_lpt, kMaxLpt)), o.scalar_lanes);
   const void *reg_fn = stream_fn_for(tr, buf, false, wt, res);
   if (!reg_fn) return hipErrorInvalidValue;
   c->buf = buf;
   c->wt = wt;
   c->res = res;
   c->vec = t.vec;
+  c->ragged = t.ragged;
   // B's column slice in LDS when it fits and the LDS variant keeps at least
   // as many waves on a CU as the register variant: where it needs more
   // registers per lane than its workgroup can be given (b = 4 .. 16, the
@@ -921,7 +1045,7 @@ hipError_t choose_stream(const StreamArgs &a, const StreamOptions &o, StreamChoi
     ColumnTiling tl = t;
     size_t lds_bytes = (size_t)a.B_rows * (size_t)tl.width * sizeof(float);
     if (hard && lds_bytes > kMaxLdsB && t.vec == 4 && t.width > 32) {
-      tl = column_tiling_max(a.b, 8);
+      tl = column_tiling_max(a.b, 8, o.scalar_lanes);
       lds_bytes = (size_t)a.B_rows * (size_t)tl.width * sizeof(float);
     }
     const int blk = lds_bytes <= kMaxLdsB ? kBlockLds : kBlockLdsBig;
@@ -978,8 +1102,8 @@ std::string describe_stream(const StreamArgs &a, const StreamOptions &o) {
   StreamChoice c;
   if (choose_stream(a, o, &c) != hipSuccess) return "";
   char buf[160];
-  std::snprintf(buf, sizeof buf, "stream_kernel<%d, %d, %s, %s, %s, %s>", c.vec, c.lpt,
-                tf(c.buf), tf(c.wt), tf(c.res), tf(c.ldsb));
+  std::snprintf(buf, sizeof buf, "stream_kernel<%d, %d, %s, %s, %s, %s>",
+                c.ragged ? kRaggedLane : c.vec, c.lpt, tf(c.buf), tf(c.wt), tf(c.res), tf(c.ldsb));
   return buf;
 }
 
@@ -1008,6 +1132,16 @@ hipError_t launch_combine(const int4 *tasks, int64_t n_tasks, double *slots, int
   const dim3 grid((unsigned)blocks_for(n_tasks, kBlock / t.lpt, 0), (unsigned)t.n_slices);
   void *params[] = {&tasks, &n_tasks, &slots, &n_slots, &b, &out, &out_rows, &res, &gamma};
   return hipLaunchKernel(fn, grid, dim3(kBlock), params, 0, s);
+}
+
+hipError_t launch_fill(float *p, int64_t n, const float *res, float gamma, hipStream_t s) {
+  if (n <= 0) return hipSuccess;
+  const int64_t blocks = blocks_for(n, kBlock * 4, 0);
+  if (blocks * kBlock > (int64_t)UINT32_MAX) return hipErrorInvalidValue;  // see prefill_rows
+  void *params[] = {&p, &n, &res, &gamma};
+  const void *fn = res ? reinterpret_cast<const void *>(&fill_kernel<true>)
+                       : reinterpret_cast<const void *>(&fill_kernel<false>);
+  return hipLaunchKernel(fn, dim3((unsigned)blocks), dim3(kBlock), params, 0, s);
 }
 
 hipError_t launch_tail(const TailArgs &args, hipStream_t s) {
