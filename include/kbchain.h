@@ -22,9 +22,11 @@
  * Streams and memory: every call only enqueues work on `stream` (hipStream_t,
  * NULL = null stream), allocates nothing and returns.  All pointers are
  * DEVICE pointers; input and output arrays must not overlap unless stated.
- * The kernels are sized for chain-harness shapes: one 1024-thread workgroup
- * reduces 16 columns over all n rows (64 rows at a time, four deep in
- * flight), so a launch spans ceil(b / 16) workgroups.
+ * A workgroup reduces 4 or 16 columns over all n rows.  Columns of more than a
+ * few thousand rows are better cut into ranges of rows, whose partial values
+ * need device scratch: the *_scratch forms take it (kbc_scratch_size bytes, 8-byte
+ * aligned, used by that call alone until it has run), and are the plain forms
+ * when it is NULL.
  *
  * Errors: arguments are checked before anything is enqueued; on failure
  * nothing is launched.  Returns KBC_OK, KBC_EINVAL (null pointer, n < 1 or
@@ -33,6 +35,7 @@
 #ifndef KBCHAIN_H
 #define KBCHAIN_H
 
+#include <stddef.h>
 #include <stdint.h>
 
 #ifdef __cplusplus
@@ -70,6 +73,23 @@ kbc_status kbc_l1_normalize_backward(int64_t n, int32_t b, const float *x, const
  * (softmax(z) - t) / b). */
 kbc_status kbc_softmax_xent(int64_t n, int32_t b, const float *z, const float *t,
                             double *col_loss, double *loss, float *dz, void *stream);
+
+/* Scratch that the *_scratch forms use at this shape (0: none; any pointer,
+ * NULL too, gives the plain form then).  A non-NULL scratch of fewer bytes is
+ * KBC_EINVAL. */
+size_t kbc_scratch_size(int64_t n, int32_t b);
+kbc_status kbc_softmax_scratch(int64_t n, int32_t b, const float *z, float *p, void *scratch,
+                               size_t bytes, void *stream);
+kbc_status kbc_softmax_backward_scratch(int64_t n, int32_t b, const float *p, const float *dp,
+                                        float *dz, void *scratch, size_t bytes, void *stream);
+kbc_status kbc_l1_normalize_scratch(int64_t n, int32_t b, const float *u, float *x, double *sums,
+                                    void *scratch, size_t bytes, void *stream);
+kbc_status kbc_l1_normalize_backward_scratch(int64_t n, int32_t b, const float *x,
+                                             const double *sums, const float *dx, float *du,
+                                             void *scratch, size_t bytes, void *stream);
+kbc_status kbc_softmax_xent_scratch(int64_t n, int32_t b, const float *z, const float *t,
+                                    double *col_loss, double *loss, float *dz, void *scratch,
+                                    size_t bytes, void *stream);
 
 #ifdef __cplusplus
 }

@@ -20,13 +20,26 @@ if not os.path.exists(LIB_PATH):
                       "(or __graft_entry__.build()) first")
 _lib = ctypes.CDLL(LIB_PATH)
 _P, _I64, _I32 = ctypes.c_void_p, ctypes.c_int64, ctypes.c_int32
+_SZ = ctypes.c_size_t
+# (The plain forms, without scratch, are not called here.)
 _lib.kbc_softmax.argtypes = [_I64, _I32, _P, _P, _P]
 _lib.kbc_softmax_backward.argtypes = [_I64, _I32, _P, _P, _P, _P]
 _lib.kbc_l1_normalize.argtypes = [_I64, _I32, _P, _P, _P, _P]
 _lib.kbc_l1_normalize_backward.argtypes = [_I64, _I32, _P, _P, _P, _P, _P]
 _lib.kbc_softmax_xent.argtypes = [_I64, _I32, _P, _P, _P, _P, _P, _P]
-for _f in (_lib.kbc_softmax, _lib.kbc_softmax_backward, _lib.kbc_l1_normalize,
-           _lib.kbc_l1_normalize_backward, _lib.kbc_softmax_xent):
+_lib.kbc_scratch_size.argtypes = [_I64, _I32]
+_lib.kbc_scratch_size.restype = _SZ
+_softmax = _lib.kbc_softmax_scratch
+_softmax_backward = _lib.kbc_softmax_backward_scratch
+_l1_normalize = _lib.kbc_l1_normalize_scratch
+_l1_normalize_backward = _lib.kbc_l1_normalize_backward_scratch
+_softmax_xent = _lib.kbc_softmax_xent_scratch
+_softmax.argtypes = [_I64, _I32, _P, _P, _P, _SZ, _P]
+_softmax_backward.argtypes = [_I64, _I32, _P, _P, _P, _P, _SZ, _P]
+_l1_normalize.argtypes = [_I64, _I32, _P, _P, _P, _P, _SZ, _P]
+_l1_normalize_backward.argtypes = [_I64, _I32, _P, _P, _P, _P, _P, _SZ, _P]
+_softmax_xent.argtypes = [_I64, _I32, _P, _P, _P, _P, _P, _P, _SZ, _P]
+for _f in (_softmax, _softmax_backward, _l1_normalize, _l1_normalize_backward, _softmax_xent):
     _f.restype = ctypes.c_int
 
 
@@ -46,6 +59,17 @@ def _stream(t):
     return ctypes.c_void_p(torch.cuda.current_stream(t.device).cuda_stream)
 
 
+def _scratch(t):
+    """(tensor, address, bytes) of the scratch of one call over t's columns, from
+    the current stream's memory; the tensor is held until the call is enqueued."""
+    import torch
+    n = _lib.kbc_scratch_size(t.shape[0], t.shape[1])
+    if n == 0:
+        return None, None, 0
+    s = torch.empty(n // 8, dtype=torch.float64, device=t.device)
+    return s, s.data_ptr(), n
+
+
 def _ok(status, what):
     if status != 0:
         raise RuntimeError(f"{what} failed with status {status}")
@@ -56,7 +80,8 @@ def softmax(z):
     import torch
     z = _mat(z, "z")
     p = torch.empty_like(z)
-    _ok(_lib.kbc_softmax(z.shape[0], z.shape[1], z.data_ptr(), p.data_ptr(), _stream(z)),
+    held, scratch, size = _scratch(z)
+    _ok(_softmax(z.shape[0], z.shape[1], z.data_ptr(), p.data_ptr(), scratch, size, _stream(z)),
         "kbc_softmax")
     return p
 
@@ -67,8 +92,9 @@ def softmax_backward(p, dp):
     p = _mat(p, "p")
     dp = _mat(dp, "dp", p.shape)
     dz = torch.empty_like(p)
-    _ok(_lib.kbc_softmax_backward(p.shape[0], p.shape[1], p.data_ptr(), dp.data_ptr(),
-                                  dz.data_ptr(), _stream(p)), "kbc_softmax_backward")
+    held, scratch, size = _scratch(p)
+    _ok(_softmax_backward(p.shape[0], p.shape[1], p.data_ptr(), dp.data_ptr(), dz.data_ptr(),
+                          scratch, size, _stream(p)), "kbc_softmax_backward")
     return dz
 
 
@@ -78,8 +104,9 @@ def l1_normalize(u):
     u = _mat(u, "u")
     x = torch.empty_like(u)
     sums = torch.empty(u.shape[1], dtype=torch.float64, device=u.device)
-    _ok(_lib.kbc_l1_normalize(u.shape[0], u.shape[1], u.data_ptr(), x.data_ptr(),
-                              sums.data_ptr(), _stream(u)), "kbc_l1_normalize")
+    held, scratch, size = _scratch(u)
+    _ok(_l1_normalize(u.shape[0], u.shape[1], u.data_ptr(), x.data_ptr(), sums.data_ptr(),
+                      scratch, size, _stream(u)), "kbc_l1_normalize")
     return x, sums
 
 
@@ -91,8 +118,9 @@ def l1_normalize_backward(x, sums, dx):
     if sums.dtype != torch.float64 or sums.numel() != x.shape[1] or not sums.is_contiguous():
         raise ValueError("sums must be a contiguous float64 tensor of b elements")
     du = torch.empty_like(x)
-    _ok(_lib.kbc_l1_normalize_backward(x.shape[0], x.shape[1], x.data_ptr(), sums.data_ptr(),
-                                       dx.data_ptr(), du.data_ptr(), _stream(x)),
+    held, scratch, size = _scratch(x)
+    _ok(_l1_normalize_backward(x.shape[0], x.shape[1], x.data_ptr(), sums.data_ptr(),
+                               dx.data_ptr(), du.data_ptr(), scratch, size, _stream(x)),
         "kbc_l1_normalize_backward")
     return du
 
@@ -107,6 +135,8 @@ def softmax_xent(z, t):
     col = torch.empty(z.shape[1], dtype=torch.float64, device=z.device)
     loss = torch.empty((), dtype=torch.float64, device=z.device)
     dz = torch.empty_like(z)
-    _ok(_lib.kbc_softmax_xent(z.shape[0], z.shape[1], z.data_ptr(), t.data_ptr(), col.data_ptr(),
-                              loss.data_ptr(), dz.data_ptr(), _stream(z)), "kbc_softmax_xent")
+    held, scratch, size = _scratch(z)
+    _ok(_softmax_xent(z.shape[0], z.shape[1], z.data_ptr(), t.data_ptr(), col.data_ptr(),
+                      loss.data_ptr(), dz.data_ptr(), scratch, size, _stream(z)),
+        "kbc_softmax_xent")
     return loss, col, dz
