@@ -40,8 +40,9 @@ constexpr int32_t kChunkQuantum = 8;
 // rows): with Z = A the residual hop follow(X, R) + gamma * X of the
 // KB-completion chains and its dX pass (A = dY there); with any other Z the
 // accumulating follow, Z = out itself adding into the output in place (each
-// row's Z is read by the thread that then writes it).  Raw buffer loads need
-// Z = A; another Z takes the plain-load path.
+// row's Z is read by the thread that then writes it).  Raw buffer loads
+// read A and Z through one buffer over both arrays: where that span is 4 GB or
+// more, plain loads are taken.
 // At most this many chunk lists (one per XCD); see StreamArgs::list_chunk.
 constexpr int kMaxChunkLists = 8;
 

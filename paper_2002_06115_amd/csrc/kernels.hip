@@ -385,7 +385,6 @@ stream_kernel(StreamArgs a) {
   // Lanes past b read column 0 and store nothing.
   const int cl = active ? c : 0;
   const uint32_t row_bytes = (uint32_t)a.b * (uint32_t)sizeof(float);
-  const uint32_t col_bytes = (uint32_t)cl * (uint32_t)sizeof(float);
 
   // (Only used with BUF, where every table is known to be under 4 GB.)
   auto rsrc = [](const void *p, uint64_t bytes) {
@@ -398,13 +397,34 @@ stream_kernel(StreamArgs a) {
   // A too, so the record index needs a select either way, and the struct
   // addresses cost them registers).
   auto rows_rsrc = [&](const void *p, int64_t rows) {
-    return RES ? rsrc(p, (uint64_t)rows * row_bytes)
-               : __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), (short)row_bytes,
-                                                   (int)rows, kRawBufferWord3);
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), (short)row_bytes, (int)rows,
+                                             kRawBufferWord3);
   };
-  const __amdgpu_buffer_rsrc_t arsrc = rows_rsrc(a.A, a.A_rows);
-  const __amdgpu_buffer_rsrc_t brsrc = rows_rsrc(a.B, a.B_rows);
-  const __amdgpu_buffer_rsrc_t orsrc = rsrc(a.out, (uint64_t)a.out_rows * row_bytes);
+  // A residual pass reads A at triples and Z at markers with one load per
+  // entry: one raw buffer spans both arrays (under 4 GB, choose_stream).  The
+  // offsets of A's rows in it start at a_off, which col_bytes already holds --
+  // one register for every use, so the other raw buffers start as far ahead of
+  // their arrays -- and those of Z's at a_off + z_delta (modulo 2^32).
+  uint32_t a_off = 0, z_delta = 0;
+  uint64_t span_bytes = (uint64_t)a.A_rows * row_bytes;
+  if constexpr (RES && BUF) {
+    const uint64_t ap = reinterpret_cast<uintptr_t>(a.A), zp = reinterpret_cast<uintptr_t>(a.Z);
+    const uint64_t a_end = ap + (uint64_t)a.A_rows * row_bytes;
+    const uint64_t z_end = zp + (uint64_t)a.out_rows * row_bytes;
+    a_off = ap > zp ? (uint32_t)(ap - zp) : 0;
+    z_delta = (uint32_t)(zp - ap);
+    span_bytes = (a_end > z_end ? a_end : z_end) - (ap < zp ? ap : zp);
+  }
+  const uint32_t col_bytes = (uint32_t)cl * (uint32_t)sizeof(float) + a_off;
+  auto ahead = [&](const void *p, uint64_t bytes) {
+    return rsrc(static_cast<const char *>(p) - a_off, bytes + a_off);
+  };
+  const __amdgpu_buffer_rsrc_t arsrc =
+      RES ? rsrc(reinterpret_cast<const char *>(a.A) - a_off, span_bytes)
+          : rows_rsrc(a.A, a.A_rows);
+  const __amdgpu_buffer_rsrc_t brsrc =
+      RES ? ahead(a.B, (uint64_t)a.B_rows * row_bytes) : rows_rsrc(a.B, a.B_rows);
+  const __amdgpu_buffer_rsrc_t orsrc = ahead(a.out, (uint64_t)a.out_rows * row_bytes);
   const __amdgpu_buffer_rsrc_t srsrc =
       rsrc(a.slots, (uint64_t)a.n_slots * a.b * sizeof(double));
 
@@ -543,11 +563,13 @@ stream_kernel(StreamArgs a) {
             gather_row<VEC>(brsrc, run_start ? (uint32_t)KBF_CHECKED(bid, a.B_rows) : kNoRecord,
                             col_bytes, xb[u]);
         } else if constexpr (BUF) {
-          load_row_buffer<VEC>(arsrc,
-                               ((triple && !same_a) || res_row)
-                                   ? (uint32_t)KBF_CHECKED(ia, a.A_rows) * row_bytes + col_bytes
-                                   : kOutOfRange,
-                               xa[u]);
+          load_row_buffer<VEC>(
+              arsrc,
+              (triple || res_row)
+                  ? (uint32_t)KBF_CHECKED(ia, triple ? a.A_rows : a.out_rows) * row_bytes +
+                        col_bytes + (triple ? 0u : z_delta)
+                  : kOutOfRange,
+              xa[u]);
           if constexpr (!LDSB)
             load_row_buffer<VEC>(brsrc,
                                  run_start ? (uint32_t)KBF_CHECKED(bid, a.B_rows) * row_bytes +
@@ -1003,9 +1025,17 @@ hipError_t choose_stream(const StreamArgs &a, const StreamOptions &o, StreamChoi
   // 4095 floats, take plain loads.
   const uint64_t row_bytes = (uint64_t)a.b * sizeof(float);
   const uint64_t lim = kOutOfRange;
-  const bool buf = !o.plain_loads && (!a.residual || a.Z == a.A) && row_bytes <= kMaxStride &&
+  // The residual passes read A and Z through one raw buffer over both.
+  const uint64_t a0 = reinterpret_cast<uintptr_t>(a.A), z0 = reinterpret_cast<uintptr_t>(a.Z);
+  const uint64_t span = !a.residual ? 0
+                                    : std::max(a0 + (uint64_t)a.A_rows * row_bytes,
+                                               z0 + (uint64_t)a.out_rows * row_bytes) -
+                                          std::min(a0, z0);
+  const uint64_t a_off = a.residual && a0 > z0 ? a0 - z0 : 0;
+  const bool buf = !o.plain_loads && span <= lim && row_bytes <= kMaxStride &&
                    (uint64_t)a.A_rows * row_bytes <= lim &&
-                   (uint64_t)a.B_rows * row_bytes <= lim && (uint64_t)a.out_rows * row_bytes <= lim &&
+                   a_off + (uint64_t)a.B_rows * row_bytes <= lim &&
+                   a_off + (uint64_t)a.out_rows * row_bytes <= lim &&
                    (uint64_t)a.n_slots * (uint64_t)a.b * sizeof(double) <= lim;
   const bool wt = a.weights != nullptr, res = a.residual != 0;
   if (a.n_lists < 1 || a.n_lists > kMaxChunkLists || a.list_chunk[0] != 0 ||
