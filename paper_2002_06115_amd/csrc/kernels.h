@@ -17,6 +17,10 @@ struct ColumnTiling {
   int width;     // columns one group covers, lpt * vec
   int n_slices;  // ceil(b / width): grid y dimension
 };
+// Widest row that the narrow kernel takes (a lane per entry, kNarrowLanes lanes
+// per chunk).
+constexpr int kMaxNarrow = 4;
+constexpr int kNarrowLanes = 8;
 // Narrowest row that is read 4 floats per lane where b % 4 != 0.
 constexpr int kMinRagged = 5;
 ColumnTiling column_tiling(int32_t b);
@@ -83,6 +87,8 @@ struct StreamOptions {
   // rows in registers, the variant used for larger tables.
   bool b_in_lds = true;
   int n_cu = 1;  // compute units of the device, for the LDS variant's grid
+  // b <= kMaxNarrow takes the narrow kernel; off: the stream kernel's layouts.
+  bool narrow = true;
   // One float per lane wherever b % 4 != 0 (the layout of b < 5), so that the
   // two layouts can be compared.
   bool scalar_lanes = false;

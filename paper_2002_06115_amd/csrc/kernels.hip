@@ -678,6 +678,164 @@ stream_kernel(StreamArgs a) {
   }
 }
 
+// -- narrow rows -------------------------------------------------------------
+//
+// Rows of at most kMaxNarrow floats: a lane holds a whole row, so a lane per
+// chunk (the stream kernel's layout at these widths) leaves few waves to hide
+// the gathers' latency, and its entry loads, 8 bytes from 64 chunks at once,
+// touch 64 lines each.  Here 8 lanes share a chunk and every lane takes one of
+// a step's 8 entries: one coalesced entry load, one A gather and one B read per
+// 64 entries of a wave (B from LDS where its table fits), kNarrowSteps steps in
+// flight.  The step's products are summed by a segmented scan over the 8 lanes,
+// cut at its markers; a marker's lane then holds the sum of the entries before
+// it back to the previous marker and writes it, and what follows the last
+// marker goes on into the next step through lane 0.  The order of the
+// additions is fixed, so results are bitwise reproducible.
+//
+// Forward stream kernel, before (a lane per chunk) and after: 20 M triples, b =
+// 1: 260 -> 107 us; 43.7 M triples over 12.9 M entities, b = 1 / 2 / 3 / 4: 557 /
+// 490 / 604 / 603 -> 357 / 406 / 458 / 440 us.  Bound by the gathers: a line per
+// entry, about 1.2e11 a second.
+constexpr int kNarrowSteps = 4;      // in flight; twice as many for one or two floats
+constexpr int kNarrowWgs = 64;       // workgroups per CU at most, where each copies B
+constexpr size_t kNarrowLds = 20 * 1024;  // eight workgroups' B tables fit a CU
+
+template <int N>
+__device__ __forceinline__ void load_floats(const float *p, float (&v)[N]) {
+  __builtin_memcpy(v, p, N * sizeof(float));
+}
+
+// The double of the lane D below (in its row of 16), or of the mirrored lane of
+// its group of 8.
+template <int CTRL>
+__device__ __forceinline__ double dpp_double(double v) {
+  const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+  const unsigned lo = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(unsigned)u, CTRL, 0xf, 0xf, true);
+  const unsigned hi = (unsigned)__builtin_amdgcn_update_dpp(0, (int)(u >> 32), CTRL, 0xf, 0xf, true);
+  return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+constexpr int kDppRowShr = 0x110, kDppHalfMirror = 0x141;
+
+template <int N, bool WEIGHTED, bool RES, bool LDSB>
+__global__ __launch_bounds__(kBlock) void narrow_kernel(StreamArgs a) {
+  constexpr int U = N <= 2 ? 2 * kNarrowSteps : kNarrowSteps;
+  extern __shared__ float narrow_b[];  // [B_rows][N] with LDSB
+  const int l = threadIdx.x % kNarrowLanes;
+  constexpr int GPB = kBlock / kNarrowLanes;
+
+  const int nl = a.n_lists;
+  const int xl = (int)(blockIdx.x % (unsigned)nl);
+  int64_t c_begin = 0, c_end = 0;
+#pragma unroll
+  for (int i = 0; i < kMaxChunkLists; ++i)
+    if (i == xl) {
+      c_begin = a.list_chunk[i];
+      c_end = a.list_chunk[i + 1];
+    }
+  const int64_t wgs_in_list = ((int64_t)gridDim.x - xl + nl - 1) / nl;
+  const int64_t stride = wgs_in_list * GPB;
+
+  if constexpr (LDSB) {
+    for (int i = threadIdx.x; i < (int)a.B_rows * N; i += kBlock) narrow_b[i] = a.B[i];
+    __syncthreads();
+  }
+
+  const int steps = a.chunk / kNarrowLanes;
+  for (int64_t g = c_begin + (blockIdx.x / nl) * GPB + threadIdx.x / kNarrowLanes; g < c_end;
+       g += stride) {
+    const int64_t p0 = KBF_CHECKED(g, a.n / a.chunk) * a.chunk + l;
+    auto entry = [&](int s, int2 &e, float &w) {
+      if (s < steps) {
+        e = a.entries[p0 + s * kNarrowLanes];
+        if constexpr (WEIGHTED) w = a.weights[p0 + s * kNarrowLanes];
+      } else {  // past the chunk: markers of no target
+        e = make_int2(-1, INT_MIN);
+        w = 0.0f;
+      }
+    };
+    int2 next[U];
+    float wnext[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) entry(u, next[u], wnext[u]);
+    double prev[N];       // the previous step's scan
+    bool carry = false;   // its last lane's row goes on
+#pragma unroll
+    for (int v = 0; v < N; ++v) prev[v] = 0.0;
+
+    for (int s0 = 0; s0 < steps; s0 += U) {
+      int2 e[U];
+      float w[U];
+      float xa[U][N], xb[U][N];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        e[u] = next[u];
+        w[u] = wnext[u];
+        const bool triple = e[u].x >= 0;
+        const int32_t ia = triple ? (e[u].x & kIdMask) : 0;
+        const float *row = a.A + (size_t)KBF_CHECKED(ia, a.A_rows) * N;
+        if constexpr (RES)
+          if (!triple && e[u].y >= 0) row = a.Z + (size_t)KBF_CHECKED(e[u].y, a.out_rows) * N;
+        load_floats<N>(row, xa[u]);
+        const int32_t ib = triple ? (e[u].y & kIdMask) : 0;
+        if constexpr (!LDSB)
+          load_floats<N>(a.B + (size_t)KBF_CHECKED(ib, a.B_rows) * N, xb[u]);
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) entry(s0 + U + u, next[u], wnext[u]);
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const bool triple = e[u].x >= 0;
+        if constexpr (LDSB) {
+          const int32_t ib = triple ? (e[u].y & kIdMask) : 0;
+          load_floats<N>(narrow_b + (size_t)KBF_CHECKED(ib, a.B_rows) * N, xb[u]);
+        }
+        // Where the lane's segment begins: after the last marker before it.
+        const unsigned marks =
+            (unsigned)(__ballot(!triple) >> (threadIdx.x % 64 / kNarrowLanes * kNarrowLanes)) &
+            ((1u << kNarrowLanes) - 1);
+        const unsigned below = marks & ((1u << l) - 1);
+        const int start = below ? 32 - __builtin_clz(below) : 0;
+        double sum[N];
+#pragma unroll
+        for (int v = 0; v < N; ++v) {
+          double t = (double)xa[u][v];
+          if constexpr (WEIGHTED) t *= (double)w[u];
+          sum[v] = triple ? t * (double)xb[u][v] : 0.0;
+          const double c = dpp_double<kDppHalfMirror>(prev[v]);
+          sum[v] += (l == 0 && carry) ? c : 0.0;
+        }
+        const bool in1 = l - 1 >= start, in2 = l - 2 >= start, in4 = l - 4 >= start;
+#pragma unroll
+        for (int v = 0; v < N; ++v) {
+          const double t1 = dpp_double<kDppRowShr + 1>(sum[v]);
+          sum[v] += in1 ? t1 : 0.0;
+          const double t2 = dpp_double<kDppRowShr + 2>(sum[v]);
+          sum[v] += in2 ? t2 : 0.0;
+          const double t4 = dpp_double<kDppRowShr + 4>(sum[v]);
+          sum[v] += in4 ? t4 : 0.0;
+          prev[v] = sum[v];
+        }
+        carry = !(marks >> (kNarrowLanes - 1) & 1);
+        const int f = e[u].y;
+        if (!triple && f != INT_MIN) {
+          if (f >= 0) {
+            float y[N];
+#pragma unroll
+            for (int v = 0; v < N; ++v)
+              y[v] = (float)(RES ? sum[v] + (double)a.gamma * (double)xa[u][v] : sum[v]);
+            float *out = a.out + (size_t)KBF_CHECKED(f, a.out_rows) * N;
+            __builtin_memcpy(out, y, N * sizeof(float));
+          } else {
+            double *slot = a.slots + (size_t)KBF_CHECKED(-(f + 1), a.n_slots) * N;
+#pragma unroll
+            for (int v = 0; v < N; ++v) slot[v] = sum[v];
+          }
+        }
+      }
+    }
+  }
+}
+
 // Adds slots [first, first + n) in increasing order; writes the float row or
 // a next-level slot.  `block` of `n_blocks` blocks share the tasks.
 template <int VEC, int LPT, bool RAGGED>
@@ -922,6 +1080,25 @@ const void *stream_fn_for(const ColumnTiling &t, bool buf, bool lds, bool wt, bo
              : stream_fn_sel<1, true, false>(t.lpt, wt, res);
 }
 
+template <int N, bool LDSB>
+const void *narrow_fn(bool wt, bool res) {
+  if (wt)
+    return res ? reinterpret_cast<const void *>(&narrow_kernel<N, true, true, LDSB>)
+               : reinterpret_cast<const void *>(&narrow_kernel<N, true, false, LDSB>);
+  return res ? reinterpret_cast<const void *>(&narrow_kernel<N, false, true, LDSB>)
+             : reinterpret_cast<const void *>(&narrow_kernel<N, false, false, LDSB>);
+}
+
+const void *narrow_fn_for(int32_t b, bool lds, bool wt, bool res) {
+  switch (b) {
+    case 1: return lds ? narrow_fn<1, true>(wt, res) : narrow_fn<1, false>(wt, res);
+    case 2: return lds ? narrow_fn<2, true>(wt, res) : narrow_fn<2, false>(wt, res);
+    case 3: return lds ? narrow_fn<3, true>(wt, res) : narrow_fn<3, false>(wt, res);
+    case 4: return lds ? narrow_fn<4, true>(wt, res) : narrow_fn<4, false>(wt, res);
+  }
+  return nullptr;
+}
+
 // Workgroups of `fn` (`block` threads, lds_bytes of dynamic LDS) that fit
 // one CU at once, from the runtime's occupancy calculator; cached per kernel,
 // block and LDS size.  0 when the query fails.
@@ -1014,7 +1191,7 @@ struct StreamChoice {
   int block = 0;
   size_t lds_bytes = 0;
   int vec = 0, lpt = 0;
-  bool ragged = false, buf = false, wt = false, res = false, ldsb = false;
+  bool narrow = false, ragged = false, buf = false, wt = false, res = false, ldsb = false;
 };
 
 hipError_t choose_stream(const StreamArgs &a, const StreamOptions &o, StreamChoice *c) {
@@ -1049,6 +1226,27 @@ hipError_t choose_stream(const StreamArgs &a, const StreamOptions &o, StreamChoi
     longest = std::max<int64_t>(longest, a.list_chunk[x + 1] - a.list_chunk[x]);
   }
   const int nl = a.n_lists;
+  if (a.b <= kMaxNarrow && o.narrow) {
+    const size_t table = (size_t)a.B_rows * (size_t)a.b * sizeof(float);
+    const bool lds = o.b_in_lds && table <= kNarrowLds;
+    constexpr int64_t groups = kBlock / kNarrowLanes;
+    int64_t per_list = std::max<int64_t>(1, (longest + groups - 1) / groups);
+    // With B in LDS each workgroup copies it, so there are only so many (eight
+    // rounds of those the CUs hold at once; one round was 4 % slower).
+    if (lds) per_list = std::min(per_list, std::max<int64_t>(1, (int64_t)kNarrowWgs * std::max(1, o.n_cu) / nl));
+    if (per_list * nl > (int64_t)INT32_MAX) return hipErrorInvalidValue;
+    c->fn = narrow_fn_for(a.b, lds, wt, res);
+    if (!c->fn) return hipErrorInvalidValue;
+    c->grid = dim3((unsigned)(per_list * nl));
+    c->block = kBlock;
+    c->lds_bytes = lds ? table : 0;
+    c->vec = a.b;
+    c->wt = wt;
+    c->res = res;
+    c->ldsb = lds;
+    c->narrow = true;
+    return hipSuccess;
+  }
   // The register variant's lane groups: at most o.max_lpt lanes wide.
   const ColumnTiling tr =
       column_tiling_max(a.b, std::max(1, std::min(o.max_lpt, kMaxLpt)), o.scalar_lanes);
@@ -1132,6 +1330,11 @@ std::string describe_stream(const StreamArgs &a, const StreamOptions &o) {
   StreamChoice c;
   if (choose_stream(a, o, &c) != hipSuccess) return "";
   char buf[160];
+  if (c.narrow) {
+    std::snprintf(buf, sizeof buf, "narrow_kernel<%d, %s, %s, %s>", c.vec, tf(c.wt), tf(c.res),
+                  tf(c.ldsb));
+    return buf;
+  }
   std::snprintf(buf, sizeof buf, "stream_kernel<%d, %d, %s, %s, %s, %s>",
                 c.ragged ? kRaggedLane : c.vec, c.lpt, tf(c.buf), tf(c.wt), tf(c.res), tf(c.ldsb));
   return buf;

@@ -69,3 +69,63 @@ def test_ragged_widths(kbf, b, weighted, path, monkeypatch):
     for name, a, c in zip(("Y", "Y residual", "Z", "dX", "dR", "dX residual", "dR residual"),
                           got, want):
         assert np.array_equal(a, c), (name, b, weighted, path)
+
+
+# The narrow kernel (a lane per entry): every width, chunks of one, several and
+# many steps, B in LDS (few relations) and not (1500 relations at b = 4; X in dR).
+@pytest.mark.parametrize("b", [1, 2, 3, 4])
+@pytest.mark.parametrize("chunk,n_r,weighted", [("8", 7, False), ("16", 7, True), ("24", 5, False),
+                                                ("40", 1500, False), ("256", 7, False),
+                                                ("256", 6000, True)])
+def test_narrow_widths(kbf, b, chunk, n_r, weighted, monkeypatch):
+    monkeypatch.setenv("KBFOLLOW_CHUNK", chunk)
+    monkeypatch.setenv("KBFOLLOW_REL_CHUNK", chunk)
+    g = np.random.default_rng(b + n_r)
+    n_e, n_t = 300, 9000
+    s = np.where(g.random(n_t) < 0.3, g.integers(0, 3, n_t), g.integers(0, n_e, n_t))
+    o = np.where(g.random(n_t) < 0.3, g.integers(0, 3, n_t), g.integers(0, n_e - 40, n_t))
+    r = g.integers(0, n_r, n_t)
+    kb_args = [a.astype(np.int32) for a in (s, r, o)]
+    w = g.uniform(0.1, 2.0, n_t).astype(np.float32) if weighted else None
+    draw = lambda n: g.standard_normal((b, n)).astype(np.float32)  # noqa: E731
+    X, R, dY, Z = draw(n_e), draw(n_r), draw(n_e), draw(n_e)
+    dev = [to_em(a) for a in (X, R, dY, Z)]
+    got = outputs(kbf, kb_args, n_e, n_r, *dev, w)
+    again = outputs(kbf, kb_args, n_e, n_r, *dev, w)
+    dXo, dRo = oracle.follow_backward(*kb_args, n_e, n_r, X, R, dY, weight=w)
+    dXr, _ = oracle.follow_backward_residual(*kb_args, n_e, n_r, X, R, dY, 0.5, weight=w)
+    Yo = oracle.follow(*kb_args, n_e, n_r, X, R, weight=w)
+    Yr = oracle.follow_residual(*kb_args, n_e, n_r, X, R, 0.5, weight=w)
+    Zo = (Yo.astype(np.float64) + 2.0 * Z).astype(np.float32)
+    for name, a, c in zip(("Y", "Y residual", "Z", "dX", "dR", "dX residual", "dR residual"), got,
+                          (Yo, Yr, Zo, dXo, dRo, dXr, dRo)):
+        # Z adds two rounded floats in the expectation: its own tolerance.
+        if name == "Z":
+            np.testing.assert_allclose(a, c, rtol=1e-5, atol=2e-6)
+        else:
+            assert_close(a, c, name)
+    for a, c in zip(got, again):
+        assert np.array_equal(a, c)
+
+
+def test_narrow_keeps_infinities_in_their_rows(kbf):
+    """A row that gathers an infinity or a NaN does not touch its neighbours in
+    the scan, and a marker's place adds nothing."""
+    n_e, n_t, b = 64, 600, 2
+    g = np.random.default_rng(5)
+    s = g.integers(0, n_e, n_t).astype(np.int32)
+    o = np.sort(g.integers(0, n_e, n_t)).astype(np.int32)
+    r = g.integers(0, 3, n_t).astype(np.int32)
+    X = g.random((b, n_e)).astype(np.float32) + 0.5
+    X[0, 7], X[1, 9] = np.inf, np.nan
+    R = g.random((b, 3)).astype(np.float32) + 0.5
+    kb = kbf.KB(s, r, o, n_e, 3)
+    Y = from_em(kb.follow(to_em(X), to_em(R)))
+    kb.close()
+    want = np.zeros((b, n_e))
+    for l in range(n_t):
+        want[:, o[l]] += X[:, s[l]].astype(np.float64) * R[:, r[l]]
+    assert np.array_equal(np.isfinite(Y), np.isfinite(want))
+    assert np.array_equal(np.isnan(Y), np.isnan(want))
+    ok = np.isfinite(want)
+    np.testing.assert_allclose(Y[ok], want[ok], rtol=1e-6)
