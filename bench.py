@@ -117,7 +117,7 @@ def mangled_name(short):
     enc = "".join(f"Lb{1 if a == 'true' else 0}E" if a in ("true", "false") else f"Li{a.replace('-', 'n')}E"
                   for a in args)
     params = {"stream_kernel": "NS_10StreamArgsE", "tail_kernel": "NS_8TailArgsE",
-              "combine_kernel": "PK15HIP_vector_typeIiLj4EElPdliPflPKff"}.get(name)
+              "combine_kernel": "NS_8TailArgsE"}.get(name)
     if params is None:
         return None
     return f"_ZN3kbf12_GLOBAL__N_1{len(name)}{name}I{enc}EEv{params}"

@@ -49,6 +49,7 @@ struct DevLayout {
   int64_t n_empty = 0;        // rows in those pieces
   int4 *ctasks = nullptr;     // all combine levels, back to back
   std::vector<int64_t> level_begin;  // host: level L is [level_begin[L], level_begin[L+1])
+  std::vector<int64_t> level_wide;   // of which the first level_wide[L] are wide tasks
   int64_t n_slots = 0;
   int64_t n_split_rows = 0;
   int64_t max_row_len = 0;
@@ -161,8 +162,10 @@ kb_status build_device_layout(kb_t *kb, DevLayout &D, int64_t rows, const PlanHo
   static_assert(sizeof(EmptyPiece) == sizeof(int2), "empty-piece layout");
   std::vector<int4> ctasks;
   D.level_begin.assign(1, 0);
-  for (const auto &lv : P.levels) {
-    for (const CombineTask &c : lv) ctasks.push_back(make_int4(c.first, c.n, c.dst, 0));
+  for (size_t L = 0; L < P.levels.size(); ++L) {
+    for (const auto *lv : {&P.wide[L], &P.levels[L]})
+      for (const CombineTask &c : *lv) ctasks.push_back(make_int4(c.first, c.n, c.dst, 0));
+    D.level_wide.push_back((int64_t)P.wide[L].size());
     D.level_begin.push_back((int64_t)ctasks.size());
   }
   kb_status st;
@@ -308,8 +311,9 @@ kb_status run_pass(const kb_t *kb, const DevLayout &D, int ph_base, const float 
     // The first combine level and the empty rows share one launch.
     PhaseScope scope(kb, ph_base + 1, s);
     const int64_t n0 = D.level_begin.size() > 1 ? D.level_begin[1] - D.level_begin[0] : 0;
-    TailArgs t{D.ctasks, n0, slots, D.n_slots, D.empty, prefill ? 0 : D.n_empty_pieces, b, out,
-               D.rows, res, gamma, 0};
+    const int64_t w0 = n0 > 0 ? D.level_wide[0] : 0;
+    TailArgs t{D.ctasks, n0, w0, slots, D.n_slots, D.empty, prefill ? 0 : D.n_empty_pieces, b, out,
+               D.rows, res, gamma, 0, 0};
     hipError_t e = launch_tail(t, s);
     if (e != hipSuccess) return hip_fail(e, "combine and empty-row kernel launch");
   }
@@ -317,8 +321,8 @@ kb_status run_pass(const kb_t *kb, const DevLayout &D, int ph_base, const float 
     PhaseScope scope(kb, ph_base + 2, s);
     for (size_t L = 1; L + 1 < D.level_begin.size(); ++L) {
       const int64_t n = D.level_begin[L + 1] - D.level_begin[L];
-      hipError_t e = launch_combine(D.ctasks + D.level_begin[L], n, slots, D.n_slots, b, out,
-                                    D.rows, res, gamma, s);
+      hipError_t e = launch_combine(D.ctasks + D.level_begin[L], n, D.level_wide[L], slots,
+                                    D.n_slots, b, out, D.rows, res, gamma, s);
       if (e != hipSuccess) return hip_fail(e, "combine kernel launch");
     }
   }
@@ -471,6 +475,11 @@ kb_status kb_create(int64_t n_entities, int64_t n_relations, int64_t n_triples,
     const int32_t chunk_rel = whole_steps(env_int(
         "KBFOLLOW_REL_CHUNK", std::min<int32_t>(128, default_chunk(n_triples + n_relations))));
     const int32_t fan_in = std::max(2, env_int("KBFOLLOW_FAN_IN", 32));
+    // Wide tasks of up to 1024 partials, so that rows of up to a million
+    // triples need two combine levels at most (none beyond the tail launch up
+    // to 1024 partials).  A fan-in set for tests keeps every task to it.
+    const int32_t wide = env_int("KBFOLLOW_WIDE", env_int("KBFOLLOW_FAN_IN", 0) > 0 ? 0 : 1024);
+    const bool pack = env_int("KBFOLLOW_PACK", 1) != 0;
     {
       LayoutHost H[3];
       const char *how = std::getenv("KBFOLLOW_LAYOUT_SORT");
@@ -526,6 +535,8 @@ kb_status kb_create(int64_t n_entities, int64_t n_relations, int64_t n_triples,
           po.class_by_b = k == BY_REL && dr_class_b;
           po.n_ids_b = n_entities;  // subjects (dR)
           po.a_blocks = k == BY_REL ? dr_blocks : 0;
+          po.wide = wide;
+          po.pack = pack;
           P[k] = plan_layout(H[k], po);
           H[k] = LayoutHost{H[k].rows};  // the sorted rows are no longer needed
         } catch (...) {
@@ -801,8 +812,8 @@ kb_status kb_phase_kernel(const kb_t *kb, int32_t b, int32_t phase, int32_t resi
       out = describe_stream(a, o);
     } else if (step == 1) {
       const int64_t n0 = D.level_begin.size() > 1 ? D.level_begin[1] - D.level_begin[0] : 0;
-      TailArgs t{D.ctasks, n0, nullptr, D.n_slots, D.empty, D.n_empty_pieces, b, A, D.rows,
-                 res ? A : nullptr, 1.0f, 0};
+      TailArgs t{D.ctasks, n0, 0, nullptr, D.n_slots, D.empty, D.n_empty_pieces, b, A, D.rows,
+                 res ? A : nullptr, 1.0f, 0, 0};
       out = describe_tail(t);
     } else if (D.level_begin.size() > 2) {
       out = describe_combine(b);

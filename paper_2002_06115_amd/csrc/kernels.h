@@ -104,20 +104,22 @@ hipError_t launch_stream(const StreamArgs &a, const StreamOptions &o, hipStream_
 // launched.  Likewise for launch_tail and launch_combine.
 std::string describe_stream(const StreamArgs &a, const StreamOptions &o);
 
-// Sums workspace slots in order (one combine level).  A final row write adds
-// gamma * res[row] when res is not null (residual hop, accumulating follow;
-// res may be out itself).
-hipError_t launch_combine(const int4 *tasks, int64_t n_tasks, double *slots, int64_t n_slots,
-                          int32_t b, float *out, int64_t out_rows, const float *res, float gamma,
-                          hipStream_t s);
+// Sums workspace slots (one combine level): the first n_wide tasks are wide
+// ones, a workgroup each, the others go to one lane group each.  A final row
+// write adds gamma * res[row] when res is not null (residual hop, accumulating
+// follow; res may be out itself).
+hipError_t launch_combine(const int4 *tasks, int64_t n_tasks, int64_t n_wide, double *slots,
+                          int64_t n_slots, int32_t b, float *out, int64_t out_rows,
+                          const float *res, float gamma, hipStream_t s);
 
 // One launch for a pass's first combine level (tasks of that level, as for
 // launch_combine) and its empty rows: +0.0 to the rows of out in the pieces
 // (first row, count), or gamma * res[row] when res is not null (residual
-// hop).  combine_blocks is set by the launcher.
+// hop).  wide_blocks and combine_blocks are set by the launcher.
 struct TailArgs {
   const int4 *tasks;
-  int64_t n_tasks;
+  int64_t n_tasks;  // of which the first n_wide are wide
+  int64_t n_wide;
   double *slots;
   int64_t n_slots;
   const int2 *pieces;
@@ -127,6 +129,7 @@ struct TailArgs {
   int64_t out_rows;
   const float *res;
   float gamma;
+  int64_t wide_blocks;
   int64_t combine_blocks;
 };
 hipError_t launch_tail(const TailArgs &a, hipStream_t s);

@@ -888,6 +888,66 @@ __device__ __forceinline__ void combine_tasks(const int4 *__restrict__ tasks, in
   }
 }
 
+// A wide combine task: one workgroup adds slots [first, first + n) of up to 32
+// columns.  Its lane groups (of at most 8 lanes, so 32 of them or more) take
+// every GPB-th slot each, eight loads in flight, and the first one adds the
+// groups' sums in order: a thousand slots in about four rounds of loads, where
+// tasks of 32 slots took two launches more for a hub row.
+constexpr int kWideLpt = 8;
+template <int VEC, int LPT, bool RAGGED>
+__device__ __forceinline__ void combine_wide(const TailArgs &a, int64_t block) {
+  constexpr int WL = LPT < kWideLpt ? LPT : kWideLpt;
+  constexpr int W = WL * VEC;
+  constexpr int GPB = kBlock / WL;
+  __shared__ double part[GPB][W];
+  const int lane = threadIdx.x % WL, grp = threadIdx.x / WL;
+  const int slices = (a.b + W - 1) / W;
+  const int c0 = (int)(block % slices) * W + lane * VEC;
+  const bool active = c0 < a.b;
+  const int c = active ? lane_cols<RAGGED>(c0, a.b).c : 0;
+  const int skip = active ? lane_cols<RAGGED>(c0, a.b).skip : 0;
+  const size_t bb = (size_t)a.b;
+  const int4 tk = a.tasks[block / slices];  // first, n, dst
+  double acc[VEC];
+#pragma unroll
+  for (int v = 0; v < VEC; ++v) acc[v] = 0.0;
+  for (int i = grp; i < tk.y; i += GPB * kUnroll) {
+    double p[kUnroll][VEC];
+#pragma unroll
+    for (int u = 0; u < kUnroll; ++u)
+      load_slot<VEC>(a.slots + (size_t)KBF_CHECKED(tk.x + min(i + u * GPB, tk.y - 1), a.n_slots) * bb + c,
+                     p[u]);
+#pragma unroll
+    for (int u = 0; u < kUnroll; ++u)
+      if (i + u * GPB < tk.y) {
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) acc[v] += p[u][v];
+      }
+  }
+#pragma unroll
+  for (int v = 0; v < VEC; ++v) part[grp][lane * VEC + v] = acc[v];
+  __syncthreads();
+  if (grp != 0 || !active) return;
+#pragma unroll
+  for (int v = 0; v < VEC; ++v) acc[v] = 0.0;
+  for (int k = 0; k < GPB; ++k)
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) acc[v] += part[k][lane * VEC + v];
+  if (tk.z >= 0) {
+    const size_t row = (size_t)KBF_CHECKED(tk.z, a.out_rows);
+    if (a.res) {
+      float r[VEC];
+      load_row<VEC>(a.res + row * bb + c, r);
+#pragma unroll
+      for (int v = 0; v < VEC; ++v) acc[v] += (double)a.gamma * (double)r[v];
+    }
+    store_row_from<VEC>(a.out + row * bb + c, acc, skip);
+  } else {
+    store_slot_from<VEC>(a.slots + (size_t)KBF_CHECKED(-(int64_t)tk.z - 1, a.n_slots) * bb + c, acc,
+                         skip);
+  }
+}
+
 // Writes the rows no triple reaches, given as pieces of consecutive rows
 // (first, count); lanes over the columns as in the stream kernel.  PACKED: a
 // lane group writes LPT consecutive pieces, whose descriptors its lanes fetch
@@ -998,36 +1058,43 @@ __global__ __launch_bounds__(kBlock) void fill_kernel(float *__restrict__ p, int
   }
 }
 
+// The blocks of a combine launch: blocks [0, wide_blocks) of the first slice
+// take the wide tasks (and their slices), the next combine_blocks the others;
+// true for the blocks after them.
+template <int VEC, int LPT, bool RAGGED>
+__device__ __forceinline__ bool combine_launch(const TailArgs &a) {
+  if ((int64_t)blockIdx.x < a.wide_blocks) {
+    if (blockIdx.y == 0) combine_wide<VEC, LPT, RAGGED>(a, blockIdx.x);
+    return false;
+  }
+  const int64_t block = (int64_t)blockIdx.x - a.wide_blocks;
+  if (block >= a.combine_blocks) return true;
+  combine_tasks<VEC, LPT, RAGGED>(a.tasks + a.n_wide, a.n_tasks - a.n_wide, a.slots, a.n_slots, a.b,
+                                  a.out, a.out_rows, a.res, a.gamma, block, a.combine_blocks);
+  return false;
+}
+
 // A later combine level.
 template <int VEC, int LPT>
-__global__ __launch_bounds__(kBlock) void combine_kernel(const int4 *__restrict__ tasks,
-                                                         int64_t n_tasks,
-                                                         double *__restrict__ slots,
-                                                         int64_t n_slots, int32_t b,
-                                                         float *out, int64_t out_rows,
-                                                         const float *res, float gamma) {
-  if (VEC == 4 && b % 4 != 0)
-    combine_tasks<VEC, LPT, VEC == 4>(tasks, n_tasks, slots, n_slots, b, out, out_rows, res, gamma,
-                                      blockIdx.x, gridDim.x);
+__global__ __launch_bounds__(kBlock) void combine_kernel(TailArgs a) {
+  if (VEC == 4 && a.b % 4 != 0)
+    combine_launch<VEC, LPT, VEC == 4>(a);
   else
-    combine_tasks<VEC, LPT, false>(tasks, n_tasks, slots, n_slots, b, out, out_rows, res, gamma,
-                                   blockIdx.x, gridDim.x);
+    combine_launch<VEC, LPT, false>(a);
 }
 
 template <int VEC, int LPT, bool PACKED, bool RAGGED>
 __device__ __forceinline__ void tail_blocks(const TailArgs &a) {
-  if ((int64_t)blockIdx.x < a.combine_blocks)
-    combine_tasks<VEC, LPT, RAGGED>(a.tasks, a.n_tasks, a.slots, a.n_slots, a.b, a.out, a.out_rows,
-                                    a.res, a.gamma, blockIdx.x, a.combine_blocks);
-  else
+  if (combine_launch<VEC, LPT, RAGGED>(a)) {
+    const int64_t before = a.wide_blocks + a.combine_blocks;
     zero_pieces<VEC, LPT, PACKED, RAGGED>(a.pieces, a.n_pieces, a.b, a.out, a.out_rows, a.res,
-                                          a.gamma, (int64_t)blockIdx.x - a.combine_blocks,
-                                          (int64_t)gridDim.x - a.combine_blocks);
+                                          a.gamma, (int64_t)blockIdx.x - before,
+                                          (int64_t)gridDim.x - before);
+  }
 }
 
-// The first combine level and the empty rows in one launch: blocks
-// [0, combine_blocks) take the combine tasks, the others the empty-row
-// pieces.  The two write disjoint rows; the combine's dependent slot reads
+// The first combine level and the empty rows in one launch: the first blocks
+// take the combine tasks, the others the empty-row pieces.  The two write disjoint rows; the combine's dependent slot reads
 // overlap with the fill's stores instead of forming a launch of their own.
 template <int VEC, int LPT, bool PACKED>
 __global__ __launch_bounds__(kBlock) void tail_kernel(TailArgs a) {
@@ -1355,15 +1422,25 @@ std::string describe_combine(int32_t b) {
   return buf;
 }
 
-hipError_t launch_combine(const int4 *tasks, int64_t n_tasks, double *slots, int64_t n_slots,
-                          int32_t b, float *out, int64_t out_rows, const float *res, float gamma,
-                          hipStream_t s) {
+// Blocks of the wide and the other combine tasks of a launch.
+static void combine_grid(TailArgs *a, const ColumnTiling &t) {
+  const int w = std::min(t.lpt, kWideLpt) * t.vec;  // columns of a wide task's workgroup
+  a->wide_blocks = a->n_wide * ((a->b + w - 1) / w);
+  a->combine_blocks =
+      a->n_tasks > a->n_wide ? blocks_for(a->n_tasks - a->n_wide, kBlock / t.lpt, 0) : 0;
+}
+
+hipError_t launch_combine(const int4 *tasks, int64_t n_tasks, int64_t n_wide, double *slots,
+                          int64_t n_slots, int32_t b, float *out, int64_t out_rows,
+                          const float *res, float gamma, hipStream_t s) {
   if (n_tasks == 0) return hipSuccess;
   const ColumnTiling t = column_tiling(b);
   const void *fn = t.vec == 4 ? combine_fn<4>(t.lpt) : combine_fn<1>(t.lpt);
   if (!fn) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)blocks_for(n_tasks, kBlock / t.lpt, 0), (unsigned)t.n_slices);
-  void *params[] = {&tasks, &n_tasks, &slots, &n_slots, &b, &out, &out_rows, &res, &gamma};
+  TailArgs a{tasks, n_tasks, n_wide, slots, n_slots, nullptr, 0, b, out, out_rows, res, gamma, 0, 0};
+  combine_grid(&a, t);
+  const dim3 grid((unsigned)(a.wide_blocks + a.combine_blocks), (unsigned)t.n_slices);
+  void *params[] = {&a};
   return hipLaunchKernel(fn, grid, dim3(kBlock), params, 0, s);
 }
 
@@ -1387,13 +1464,14 @@ hipError_t launch_tail(const TailArgs &args, hipStream_t s) {
   TailArgs a = args;
   // One combine task per lane group.  Empty rows, packed: LPT pieces per
   // lane group, 256 per block; residual: kFillPieces pieces per lane group.
-  a.combine_blocks = a.n_tasks > 0 ? blocks_for(a.n_tasks, kBlock / t.lpt, 0) : 0;
+  combine_grid(&a, t);
   const int64_t zero_blocks =
       a.n_pieces > 0
           ? blocks_for(a.n_pieces, packed ? kBlock : (kBlock / t.lpt) * kFillPieces, 0)
           : 0;
-  if (a.combine_blocks + zero_blocks > (int64_t)INT32_MAX) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)(a.combine_blocks + zero_blocks), (unsigned)t.n_slices);
+  const int64_t blocks = a.wide_blocks + a.combine_blocks + zero_blocks;
+  if (blocks > (int64_t)INT32_MAX) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)blocks, (unsigned)t.n_slices);
   void *params[] = {&a};
   return hipLaunchKernel(fn, grid, dim3(kBlock), params, 0, s);
 }

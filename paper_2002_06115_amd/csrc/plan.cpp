@@ -15,6 +15,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <cstddef>
 #include <cstdlib>
 #include <cstdio>
 #include <exception>
@@ -574,7 +575,7 @@ PlanHost plan_layout(const LayoutHost &L, const PlanOptions &opt) {
       pend.push_back({row, x, idx, (int64_t)E.size()});
       marker(kNoTarget);  // target set when the slots are numbered
     };
-    for (const Seg &g : segs[x]) {
+    auto emit = [&](const Seg &g) {
       int32_t parts = 0;
       bool pending = false;  // triples of this segment since the last marker
       int32_t prev_b = 0, prev_a = -1;
@@ -613,6 +614,35 @@ PlanHost plan_layout(const LayoutHost &L, const PlanOptions &opt) {
         slot_marker(g.row, parts++);
       else
         marker(g.row);
+    };
+    if (!opt.pack) {
+      for (const Seg &g : segs[x]) emit(g);
+    } else {
+      // Segments in order, but one that would cross the chunk's end although
+      // a chunk could hold it waits (at most kPackWindow of them) for the next
+      // chunk, while later ones that fit are placed.
+      constexpr size_t kPackWindow = 32;
+      std::vector<size_t> wait;
+      size_t next = 0;
+      while (next < segs[x].size() || !wait.empty()) {
+        while (wait.size() < kPackWindow && next < segs[x].size()) wait.push_back(next++);
+        const int64_t room = chunk - (int64_t)E.size() % chunk;
+        size_t pick = wait.size();
+        for (size_t i = 0; i < wait.size() && pick == wait.size(); ++i) {
+          const Seg &g = segs[x][wait[i]];
+          const int64_t need = g.end - g.beg + 1;
+          if (need > chunk || need <= room) pick = i;  // longer than a chunk: crosses anyway
+        }
+        if (pick == wait.size()) {
+          if (room <= chunk / 8) {
+            for (int64_t i = 0; i < room; ++i) marker(kNoTarget);
+            continue;
+          }
+          pick = 0;
+        }
+        emit(segs[x][wait[pick]]);
+        wait.erase(wait.begin() + (std::ptrdiff_t)pick);
+      }
     }
     // Pad with no-op markers to whole chunks: every lane group then walks
     // exactly `chunk` entries.
@@ -680,27 +710,33 @@ PlanHost plan_layout(const LayoutHost &L, const PlanOptions &opt) {
   }
   P.n_chunks = (int64_t)P.entries.size() / chunk;
 
-  // Combine levels: a row split into n partials is reduced fan_in slots at a
-  // time until one task writes the row.
+  // Combine levels: a row split into n partials is reduced up to fan_in slots
+  // (or `wide`, by a wide task) at a time until one task writes the row.
+  auto add = [&](size_t level, bool wide, const CombineTask &task) {
+    if (P.levels.size() <= level) {
+      P.levels.resize(level + 1);
+      P.wide.resize(level + 1);
+    }
+    (wide ? P.wide : P.levels)[level].push_back(task);
+  };
   for (const Split &sp : splits) {
     int64_t first_slot = sp.first, cnt = sp.n;
     size_t level = 0;
-    while (cnt > fan_in) {
-      const int64_t groups = (cnt + fan_in - 1) / fan_in;
+    const int64_t most = opt.wide > fan_in ? opt.wide : fan_in;
+    while (cnt > most) {
+      const int64_t groups = (cnt + most - 1) / most;
       const int64_t out0 = P.n_slots;
       P.n_slots += groups;
-      if (P.levels.size() <= level) P.levels.resize(level + 1);
       for (int64_t g = 0; g < groups; ++g) {
-        const int64_t m = std::min<int64_t>(fan_in, cnt - g * fan_in);
-        P.levels[level].push_back({(int32_t)(first_slot + g * fan_in), (int32_t)m,
-                                   (int32_t)(-(out0 + g) - 1), 0});
+        const int64_t m = std::min<int64_t>(most, cnt - g * most);
+        add(level, m > fan_in, {(int32_t)(first_slot + g * most), (int32_t)m,
+                                (int32_t)(-(out0 + g) - 1), 0});
       }
       first_slot = out0;
       cnt = groups;
       ++level;
     }
-    if (P.levels.size() <= level) P.levels.resize(level + 1);
-    P.levels[level].push_back({(int32_t)first_slot, (int32_t)cnt, sp.row, 0});
+    add(level, cnt > fan_in, {(int32_t)first_slot, (int32_t)cnt, sp.row, 0});
   }
   return P;
 }

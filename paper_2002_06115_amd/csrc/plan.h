@@ -21,7 +21,8 @@ namespace kbf {
 
 enum LayoutKind { BY_OBJ = 0, BY_SUBJ = 1, BY_REL = 2 };
 
-// Sum slots [first, first + n) in order into dst (row if >= 0, else slot -(dst + 1)).
+// Sum slots [first, first + n) into dst (row if >= 0, else slot -(dst + 1)), in
+// order, or, a wide task, as a workgroup adds them (combine_wide in kernels.hip).
 struct CombineTask {
   int32_t first, n, dst, pad;
 };
@@ -107,6 +108,17 @@ struct PlanOptions {
   // ranges (0 or 1: no blocks), so that with band the chunks of a list walk
   // the gathered table one block at a time.
   int32_t a_blocks = 0;
+  // Above fan_in: rows (and levels) of more than fan_in partials are combined by
+  // wide tasks of up to this many, a workgroup each (0: none).
+  int32_t wide = 0;
+  // Small rows are placed so that few of them cross a chunk's end: where the
+  // next one does not fit, the first of the following ones that does goes
+  // there, or, if at most chunk / 8 entries are left, no-op markers do.  (Rows
+  // split over two partials on a KB of 43 k entities and 190 k triples, 16-entry
+  // chunks: 5700 -> 550, the first combine level 8.4 -> 5.5 us at b = 128; 10 M
+  // entities, 50 M triples: 73 k -> 13 k, partial slots 345 k -> 201 k, step
+  // 2.500 -> 2.436 ms; grid of 10^6 cells 707 -> 667 us for two hops.)
+  bool pack = false;
 };
 
 struct PlanHost {
@@ -120,6 +132,7 @@ struct PlanHost {
   std::vector<EmptyPiece> empty;    // the rows no triple reaches
   int64_t n_empty_rows = 0;
   std::vector<std::vector<CombineTask>> levels;
+  std::vector<std::vector<CombineTask>> wide;  // per level, beside levels[level]
   int64_t n_slots = 0;
   int64_t n_split_rows = 0;
   int64_t max_row_len = 0;
