@@ -94,9 +94,14 @@ typedef enum {
  * same up to the summation order of split rows, or bitwise the same):
  *   KBFOLLOW_CHUNK, KBFOLLOW_REL_CHUNK  entries per chunk of the entity and
  *                                       relation layouts (default 256 and
- *                                       128, less for small KBs; rounded up
- *                                       to 8);
- *   KBFOLLOW_FAN_IN                     partials per combine task (32);
+ *                                       128, less for small KBs and for those
+ *                                       without hubs; rounded up to 8);
+ *   KBFOLLOW_FAN_IN                     partials per combine task (32; set, it
+ *                                       turns wide tasks off);
+ *   KBFOLLOW_WIDE                       partials per wide combine task, a
+ *                                       workgroup each (1024; 0: none);
+ *   KBFOLLOW_PACK=0                     rows in order whether they cross a
+ *                                       chunk's end or not;
  *   KBFOLLOW_PLAIN_LOADS=1              plain loads instead of raw buffer
  *                                       loads (bitwise the same);
  *   KBFOLLOW_B_IN_LDS=0                 the second operand (R, or X for dR)
@@ -208,9 +213,9 @@ kb_status kb_follow_backward(const kb_t *kb, int32_t b, const float *X, const fl
  *
  * The scratch holds KB_NOALLOC_SCRATCH_BYTES (64 MiB) per GPU, taken on the
  * first call on that GPU and held until the process ends.  A KB and batch
- * size whose kb_workspace_size exceeds it are refused with KB_EINVAL before
- * anything is enqueued (the 10 M-entity / 50 M-triple KB needs about 61 MiB
- * at b = 32).  Every call on one GPU shares that GPU's scratch, and the
+ * size whose forward pass needs more (at most kb_workspace_size) are refused
+ * with KB_EINVAL before anything is enqueued (the 10 M-entity / 50 M-triple KB
+ * needs about 49 MiB at b = 32).  Every call on one GPU shares that GPU's scratch, and the
  * scratch keeps the last call's partials (each call writes every partial it
  * reads, so nothing needs clearing): calls that overlap in time on one GPU --
  * on two streams, or from two host threads -- race and must not be issued.

@@ -337,8 +337,12 @@ size_t dr_slots_offset(const kb_t *kb, int32_t b) {
   return round256((size_t)kb->L[BY_SUBJ].n_slots * (size_t)b * sizeof(double));
 }
 
+size_t forward_bytes(const kb_t *kb, int32_t b) {
+  return round256((size_t)kb->L[BY_OBJ].n_slots * (size_t)b * sizeof(double));
+}
+
 size_t workspace_bytes(const kb_t *kb, int32_t b) {
-  const size_t fwd = round256((size_t)kb->L[BY_OBJ].n_slots * (size_t)b * sizeof(double));
+  const size_t fwd = forward_bytes(kb, b);
   const size_t bwd = dr_slots_offset(kb, b) +
                      round256((size_t)kb->L[BY_REL].n_slots * (size_t)b * sizeof(double));
   return std::max(fwd, bwd);
@@ -346,9 +350,8 @@ size_t workspace_bytes(const kb_t *kb, int32_t b) {
 
 // The workspace must be big enough, aligned, and clear of every array the
 // call reads or writes (arrays[i] of bytes[i]; null entries are skipped).
-kb_status check_ws(const kb_t *kb, int32_t b, void *ws, size_t ws_bytes,
+kb_status check_ws(size_t need, void *ws, size_t ws_bytes,
                    std::initializer_list<std::pair<const void *, size_t>> arrays) {
-  const size_t need = workspace_bytes(kb, b);
   if (need == 0) return KB_OK;
   if (!ws) return fail(KB_EINVAL, "workspace is NULL but " + std::to_string(need) + " bytes are needed");
   if (ws_bytes < need)
@@ -462,18 +465,22 @@ kb_status kb_create(int64_t n_entities, int64_t n_relations, int64_t n_triples,
       while (c > 16 && entries / c < 32768) c /= 2;
       return c;
     };
+    // Down to 32 entries for 96 K chunks where at most an eighth of the triples
+    // lie in hub rows, so that shorter chunks add few partials: the rows in
+    // flight at once are then closer together, and so are what they gather in a
+    // KB with local ids (grid of 10^6 cells, b = 128, 128 -> 32 entries: 336 ->
+    // 297 us; 2 M entities and 20 M triples with uniform subjects per object, b =
+    // 1, 256 -> 128: 107 -> 105).  With hubs the partials cost more than it gives
+    // (10 M entities, b = 32, 256 -> 128: forward 786 -> 809).
+    auto entity_chunk = [&](int64_t entries, double hubs) {
+      int32_t c = default_chunk(entries);
+      while (hubs <= 0.125 && c > 32 && entries / c < 98304) c /= 2;
+      return c;
+    };
     // A chunk is a whole number of kernel steps.
     auto whole_steps = [](int32_t c) {
       return std::max(kChunkQuantum, (c + kChunkQuantum - 1) / kChunkQuantum * kChunkQuantum);
     };
-    const int32_t chunk_seg =
-        whole_steps(env_int("KBFOLLOW_CHUNK", default_chunk(n_triples + n_entities)));
-    // dR's chunks at most 128 entries: with its object blocks, the shorter
-    // chunks keep the gathers in flight at once closer together (measured on
-    // one box: 10 M-entity KB step 2.369 -> 2.340 ms, training-shaped KB
-    // 9.05 -> 9.00 ms; 64 no better), for twice the partial slots.
-    const int32_t chunk_rel = whole_steps(env_int(
-        "KBFOLLOW_REL_CHUNK", std::min<int32_t>(128, default_chunk(n_triples + n_relations))));
     const int32_t fan_in = std::max(2, env_int("KBFOLLOW_FAN_IN", 32));
     // Wide tasks of up to 1024 partials, so that rows of up to a million
     // triples need two combine levels at most (none beyond the tail launch up
@@ -487,7 +494,6 @@ kb_status kb_create(int64_t n_entities, int64_t n_relations, int64_t n_triples,
                     how && std::strcmp(how, "counting") == 0 ? LayoutSort::kCounting
                                                              : LayoutSort::kAuto);
       // The three plans on three host threads, then the uploads in turn.
-      const int32_t plen[3] = {chunk_seg, chunk_seg, chunk_rel};
       // One chunk list per XCD (8 on an MI355X; KBFOLLOW_XCD overrides, 1 is
       // a single list in row order).  Hub rows (KBFOLLOW_HUB_MIN triples or
       // more) are split by the class of the gathered id; in the forward and
@@ -496,6 +502,11 @@ kb_status kb_create(int64_t n_entities, int64_t n_relations, int64_t n_triples,
       // which keeps runs of equal subject, whose X row is read once per run.
       const int32_t n_xcd = std::max(1, std::min(kMaxXcd, env_int("KBFOLLOW_XCD", 8)));
       const int64_t hub_min = std::max(1, env_int("KBFOLLOW_HUB_MIN", 256));
+      const int64_t ent = n_triples + n_entities;
+      auto chunk_of = [&](int k) {
+        return whole_steps(
+            env_int("KBFOLLOW_CHUNK", entity_chunk(ent, hub_share(H[k].row, hub_min))));
+      };
       const bool band = env_int("KBFOLLOW_BAND", 1) != 0;
       // dR's lists are classed by subject (the X row read once per run) when
       // the objects are skewed, by the gathered object when they are not
@@ -520,6 +531,17 @@ kb_status kb_create(int64_t n_entities, int64_t n_relations, int64_t n_triples,
       // the same within 1 %); on the training-shaped KB 3.35 -> 3.04 ms with
       // object classes (16 -> 64 blocks).
       const int32_t dr_blocks = env_int("KBFOLLOW_DR_BLOCKS", 64);
+      // dR's chunks at most 128 entries: with its object blocks, the shorter
+      // chunks keep the gathers in flight at once closer together (measured on
+      // one box: 10 M-entity KB step 2.369 -> 2.340 ms, training-shaped KB 9.05
+      // -> 9.00 ms), for twice the partial slots.  64 with object classes, where
+      // one XCD's window of dY is what its L2 may hold: training-shaped KB dR
+      // with its combine 2.92 -> 2.82 ms (subject classes, 10 M-entity KB:
+      // backward 1.478 -> 1.505, not taken).
+      const int32_t chunk_rel = whole_steps(
+          env_int("KBFOLLOW_REL_CHUNK", std::min<int32_t>(dr_class_b ? 128 : 64,
+                                                          default_chunk(n_triples + n_relations))));
+      const int32_t plen[3] = {chunk_of(BY_OBJ), chunk_of(BY_SUBJ), chunk_rel};
       PlanHost P[3];
       std::exception_ptr err[3];
       auto plan = [&](int k) {
@@ -607,7 +629,8 @@ namespace {
 
 // Y = follow(X, R) [+ gamma * Z when Z is non-null].
 kb_status follow_impl(const kb_t *kb, int32_t b, const float *X, const float *R, const float *Z,
-                      float gamma, float *Y, void *workspace, size_t ws_bytes, void *stream) {
+                      float gamma, float *Y, size_t need, void *workspace, size_t ws_bytes,
+                      void *stream) {
   try {
     if (!kb) return fail(KB_EINVAL, "kb must be non-NULL");
     if (b < 1) return fail(KB_EINVAL, "b must be >= 1");
@@ -625,7 +648,7 @@ kb_status follow_impl(const kb_t *kb, int32_t b, const float *X, const float *R,
     // Y itself, but not overlap it otherwise.
     if (Z != Y && overlaps(Z, ent_bytes, Y, ent_bytes))
       return fail(KB_EINVAL, "Z overlaps Y without being Y");
-    kb_status st = check_ws(kb, b, workspace, ws_bytes,
+    kb_status st = check_ws(need, workspace, ws_bytes,
                             {{X, ent_bytes}, {R, rel_bytes}, {Y, ent_bytes}, {Z, ent_bytes}});
     if (st != KB_OK) return st;
     if ((st = check_device(kb)) != KB_OK) return st;
@@ -663,7 +686,7 @@ kb_status backward_impl(const kb_t *kb, int32_t b, const float *X, const float *
     if (want_dr && (overlaps(dR, rel_bytes, X, ent_bytes) || overlaps(dR, rel_bytes, R, rel_bytes) ||
                     overlaps(dR, rel_bytes, dY, ent_bytes)))
       return fail(KB_EINVAL, "dR overlaps another array");
-    kb_status st = check_ws(kb, b, workspace, ws_bytes,
+    kb_status st = check_ws(workspace_bytes(kb, b), workspace, ws_bytes,
                             {{X, ent_bytes}, {R, rel_bytes}, {dY, ent_bytes},
                              {want_dx ? dX : nullptr, ent_bytes}, {want_dr ? dR : nullptr, rel_bytes}});
     if (st != KB_OK) return st;
@@ -717,7 +740,8 @@ extern "C" {
 
 kb_status kb_follow(const kb_t *kb, int32_t b, const float *X, const float *R, float *Y,
                     void *workspace, size_t ws_bytes, void *stream) {
-  return follow_impl(kb, b, X, R, nullptr, 0.0f, Y, workspace, ws_bytes, stream);
+  return follow_impl(kb, b, X, R, nullptr, 0.0f, Y, kb_workspace_size(kb, b), workspace, ws_bytes,
+                     stream);
 }
 
 kb_status kb_follow_noalloc(const kb_t *kb, int32_t b, const float *X, const float *R, float *Y,
@@ -727,7 +751,7 @@ kb_status kb_follow_noalloc(const kb_t *kb, int32_t b, const float *X, const flo
   // The partials go to the library's fixed scratch instead of a workspace;
   // a KB and batch size that need more than it holds are refused before
   // anything is enqueued.
-  const size_t need = workspace_bytes(kb, b);
+  const size_t need = forward_bytes(kb, b);
   if (need > kStaticScratchBytes)
     return fail(KB_EINVAL, "kb_follow_noalloc: this KB needs " + std::to_string(need) +
                                " bytes of scratch at b = " + std::to_string(b) +
@@ -740,21 +764,23 @@ kb_status kb_follow_noalloc(const kb_t *kb, int32_t b, const float *X, const flo
     hipError_t e = static_scratch(kb->device, &ws);
     if (e != hipSuccess) return hip_fail(e, "address of the fixed scratch");
   }
-  return follow_impl(kb, b, X, R, nullptr, 0.0f, Y, ws, need > 0 ? kStaticScratchBytes : 0,
+  return follow_impl(kb, b, X, R, nullptr, 0.0f, Y, need, ws, need > 0 ? kStaticScratchBytes : 0,
                      stream);
 }
 
 kb_status kb_follow_residual(const kb_t *kb, int32_t b, const float *X, const float *R,
                              float gamma, float *Y, void *workspace, size_t ws_bytes,
                              void *stream) {
-  return follow_impl(kb, b, X, R, X, gamma, Y, workspace, ws_bytes, stream);
+  return follow_impl(kb, b, X, R, X, gamma, Y, kb_workspace_size(kb, b), workspace, ws_bytes,
+                     stream);
 }
 
 kb_status kb_follow_accumulate(const kb_t *kb, int32_t b, const float *X, const float *R,
                                const float *Z, float gamma, float *Y, void *workspace,
                                size_t ws_bytes, void *stream) {
   if (kb && kb->n_entities > 0 && !Z) return fail(KB_EINVAL, "Z must be non-NULL");
-  return follow_impl(kb, b, X, R, Z, gamma, Y, workspace, ws_bytes, stream);
+  return follow_impl(kb, b, X, R, Z, gamma, Y, kb_workspace_size(kb, b), workspace, ws_bytes,
+                     stream);
 }
 
 kb_status kb_follow_backward_residual(const kb_t *kb, int32_t b, const float *X, const float *R,

@@ -343,9 +343,15 @@ static void add_empty(PlanHost &P, int64_t first, int64_t count) {
 }
 
 // Classes of the gathered ids, about equal in the number of triples that
-// gather each: the heaviest ids one by one onto the lightest class, the
-// others by id modulo n_xcd.  Empty when the id space is far larger than the
-// KB (then the class of id a is a % n_xcd).
+// gather each: the others than the heaviest cut into n_xcd consecutive ranges
+// of equal weight, then the heaviest one by one onto the lightest class.  One
+// XCD's gathers then stay within an eighth of the table's pages (and rows that
+// are near each other in a KB with local ids meet in one L2): against ids
+// modulo n_xcd, stream kernels forward / dX / dR, us: 10 M entities, b = 32, 705
+// / 792 / 1469 -> 650 / 731 / 1431; 2 M entities, b = 256, 2036 / 2981 / 2944 ->
+// 2030 / 2811 / 2841; grid of 10^6 cells, b = 128, 363 / 363 / 549 -> 336 / 336 /
+// 427.  Empty when the id space is far larger than the KB (then the class of id
+// a is its range of the id space).
 static std::vector<uint8_t> id_classes(const std::vector<int32_t> &col, int64_t n_ids, int X) {
   const int64_t n_t = (int64_t)col.size();
   if (X <= 1 || n_ids <= 0 || n_ids > 4 * n_t + (int64_t(1) << 20)) return {};
@@ -374,10 +380,14 @@ static std::vector<uint8_t> id_classes(const std::vector<int32_t> &col, int64_t 
   std::vector<char> is_heavy(n_ids, 0);
   for (int32_t h : heavy) is_heavy[h] = 1;
   int64_t load[kMaxXcd] = {};
+  int64_t rest = 0, seen = 0;
+  for (int64_t i = 0; i < n_ids; ++i) rest += is_heavy[i] ? 0 : cnt[i];
   for (int64_t i = 0; i < n_ids; ++i)
     if (!is_heavy[i]) {
-      cls[i] = (uint8_t)(i % X);
-      load[i % X] += cnt[i];
+      const int c = (int)std::min<int64_t>(X - 1, seen * X / std::max<int64_t>(1, rest));
+      cls[i] = (uint8_t)c;
+      load[c] += cnt[i];
+      seen += cnt[i];
     }
   for (int32_t h : heavy) {
     int best = 0;
@@ -387,6 +397,16 @@ static std::vector<uint8_t> id_classes(const std::vector<int32_t> &col, int64_t 
     load[best] += cnt[h];
   }
   return cls;
+}
+
+double hub_share(const std::vector<int32_t> &row, int64_t hub_min) {
+  int64_t in_hubs = 0;
+  const int64_t n = (int64_t)row.size();
+  for (int64_t beg = 0, end; beg < n; beg = end) {
+    for (end = beg + 1; end < n && row[end] == row[beg];) ++end;
+    if (end - beg >= hub_min) in_hubs += end - beg;
+  }
+  return n ? (double)in_hubs / (double)n : 0.0;
 }
 
 double top_id_share(const std::vector<int32_t> &col, int64_t n_ids, double frac) {
@@ -441,12 +461,13 @@ PlanHost plan_layout(const LayoutHost &L, const PlanOptions &opt) {
   std::vector<int32_t> pos(n_t);
   for (int64_t i = 0; i < n_t; ++i) pos[i] = (int32_t)i;
   const std::vector<int32_t> &cls_col = opt.class_by_b ? L.col_b : L.col_a;
-  const std::vector<uint8_t> cls_tab =
-      id_classes(cls_col, opt.class_by_b ? opt.n_ids_b : opt.n_ids_a, X);
+  const int64_t cls_ids = opt.class_by_b ? opt.n_ids_b : opt.n_ids_a;
+  const std::vector<uint8_t> cls_tab = id_classes(cls_col, cls_ids, X);
   // The class of the triple at position l.
   auto cls_at = [&](int64_t l) -> int {
     const int32_t id = cls_col[l];
-    return cls_tab.empty() ? (int)(id % X) : (int)cls_tab[id];
+    if (!cls_tab.empty()) return (int)cls_tab[id];
+    return (int)std::min<int64_t>(X - 1, (int64_t)id * X / std::max<int64_t>(1, cls_ids));
   };
 
   // Segments per list: a hub row's class segments first (rows in order),

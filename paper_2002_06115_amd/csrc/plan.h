@@ -142,6 +142,9 @@ struct PlanHost {
 // ceil(frac * n_ids) most frequent ones: how skewed the id distribution is.
 double top_id_share(const std::vector<int32_t> &col, int64_t n_ids, double frac);
 
+// The share of a sorted layout's triples that lie in rows of at least hub_min.
+double hub_share(const std::vector<int32_t> &row, int64_t hub_min);
+
 // Returns "" when the triple arrays are valid, else a message; *range_error
 // tells an out-of-range id (KB_ERANGE) from any other problem (KB_EINVAL).
 std::string validate_triples(int64_t n_entities, int64_t n_relations, int64_t n_triples,
