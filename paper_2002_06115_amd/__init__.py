@@ -224,7 +224,27 @@ class KB:
 
     @staticmethod
     def _ptr(t):
-        return None if t is None else ctypes.c_void_p(t.data_ptr())
+        return None if t is None else t.data_ptr()  # an int: the C arguments are void pointers
+
+    def _enqueue(self, fn, what, stream, b, *args, scratch=True):
+        """fn(handle, b, *args[, workspace, its bytes], stream) with this KB's
+        device current (the device guard is entered only where another one is),
+        on ``stream`` or the current stream."""
+        import torch
+        index = self.device.index
+        raw = torch._C._cuda_getCurrentRawStream(index) if stream is None else stream.cuda_stream
+        if scratch:
+            ws = self._ws.get((b, raw))
+            if ws is None:
+                ws = self.workspace(b, stream)
+            args += (None, 0) if ws is None else (ws.data_ptr(), ws.numel())
+        if torch.cuda.current_device() == index:
+            status = fn(self._handle, b, *args, raw)
+        else:
+            with torch.cuda.device(self.device):
+                status = fn(self._handle, b, *args, raw)
+        if status != KB_OK:
+            _check(status, what)
 
     # -- the operations --------------------------------------------------------
     def follow(self, X, R, out=None, stream=None, residual=None):
@@ -240,19 +260,12 @@ class KB:
         if R.shape[1] != b:
             raise ValueError("X and R must have the same batch size")
         Y = torch.empty_like(X) if out is None else self._act(out, self.n_entities, "out")
-        s = torch.cuda.current_stream(self.device) if stream is None else stream
-        ws = self.workspace(b, s)
-        nws = 0 if ws is None else ws.numel()
-        with torch.cuda.device(self.device):
-            if residual is None:
-                _check(_lib.kb_follow(self._handle, b, self._ptr(X), self._ptr(R), self._ptr(Y),
-                                      self._ptr(ws), nws, ctypes.c_void_p(s.cuda_stream)),
-                       "kb_follow")
-            else:
-                _check(_lib.kb_follow_residual(self._handle, b, self._ptr(X), self._ptr(R),
-                                               float(residual), self._ptr(Y), self._ptr(ws), nws,
-                                               ctypes.c_void_p(s.cuda_stream)),
-                       "kb_follow_residual")
+        if residual is None:
+            self._enqueue(_lib.kb_follow, "kb_follow", stream, b, self._ptr(X), self._ptr(R),
+                          self._ptr(Y))
+        else:
+            self._enqueue(_lib.kb_follow_residual, "kb_follow_residual", stream, b, self._ptr(X),
+                          self._ptr(R), float(residual), self._ptr(Y))
         return Y
 
     def follow_noalloc(self, X, R, out, stream=None):
@@ -266,12 +279,8 @@ class KB:
         b = X.shape[1]
         if R.shape[1] != b or Y.shape[1] != b:
             raise ValueError("X, R and out must have the same batch size")
-        import torch
-        s = torch.cuda.current_stream(self.device) if stream is None else stream
-        with torch.cuda.device(self.device):
-            _check(_lib.kb_follow_noalloc(self._handle, b, self._ptr(X), self._ptr(R),
-                                          self._ptr(Y), ctypes.c_void_p(s.cuda_stream)),
-                   "kb_follow_noalloc")
+        self._enqueue(_lib.kb_follow_noalloc, "kb_follow_noalloc", stream, b, self._ptr(X),
+                      self._ptr(R), self._ptr(Y), scratch=False)
         return Y
 
     def follow_accumulate(self, X, R, Z, gamma=1.0, out=None, stream=None):
@@ -285,14 +294,8 @@ class KB:
         if R.shape[1] != b or Z.shape[1] != b:
             raise ValueError("X, R and Z must have the same batch size")
         Y = torch.empty_like(X) if out is None else self._act(out, self.n_entities, "out")
-        s = torch.cuda.current_stream(self.device) if stream is None else stream
-        ws = self.workspace(b, s)
-        nws = 0 if ws is None else ws.numel()
-        with torch.cuda.device(self.device):
-            _check(_lib.kb_follow_accumulate(self._handle, b, self._ptr(X), self._ptr(R),
-                                             self._ptr(Z), float(gamma), self._ptr(Y),
-                                             self._ptr(ws), nws, ctypes.c_void_p(s.cuda_stream)),
-                   "kb_follow_accumulate")
+        self._enqueue(_lib.kb_follow_accumulate, "kb_follow_accumulate", stream, b, self._ptr(X),
+                      self._ptr(R), self._ptr(Z), float(gamma), self._ptr(Y))
         return Y
 
     def follow_backward(self, X, R, dY, want_dx=True, want_dr=True, dX=None, dR=None,
@@ -313,20 +316,13 @@ class KB:
             dR = torch.empty((self.n_relations, b), dtype=torch.float32, device=self.device)
         dX = self._act(dX, self.n_entities, "dX") if want_dx else None
         dR = self._act(dR, self.n_relations, "dR") if want_dr else None
-        s = torch.cuda.current_stream(self.device) if stream is None else stream
-        ws = self.workspace(b, s)
-        nws = 0 if ws is None else ws.numel()
-        with torch.cuda.device(self.device):
-            if residual is None:
-                _check(_lib.kb_follow_backward(self._handle, b, self._ptr(X), self._ptr(R),
-                                               self._ptr(dY), self._ptr(dX), self._ptr(dR),
-                                               self._ptr(ws), nws, ctypes.c_void_p(s.cuda_stream)),
-                       "kb_follow_backward")
-            else:
-                _check(_lib.kb_follow_backward_residual(
-                    self._handle, b, self._ptr(X), self._ptr(R), self._ptr(dY), float(residual),
-                    self._ptr(dX), self._ptr(dR), self._ptr(ws), nws,
-                    ctypes.c_void_p(s.cuda_stream)), "kb_follow_backward_residual")
+        if residual is None:
+            self._enqueue(_lib.kb_follow_backward, "kb_follow_backward", stream, b, self._ptr(X),
+                          self._ptr(R), self._ptr(dY), self._ptr(dX), self._ptr(dR))
+        else:
+            self._enqueue(_lib.kb_follow_backward_residual, "kb_follow_backward_residual", stream,
+                          b, self._ptr(X), self._ptr(R), self._ptr(dY), float(residual),
+                          self._ptr(dX), self._ptr(dR))
         return dX, dR
 
     # -- event timing -----------------------------------------------------------

@@ -56,7 +56,7 @@ def _mat(t, name, shape=None):
 
 def _stream(t):
     import torch
-    return ctypes.c_void_p(torch.cuda.current_stream(t.device).cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(t.device.index)
 
 
 def _scratch(t):
