@@ -533,7 +533,7 @@ kb_status kb_create(int64_t n_entities, int64_t n_relations, int64_t n_triples,
       const int32_t dr_blocks = env_int("KBFOLLOW_DR_BLOCKS", 64);
       // dR's chunks at most 128 entries: with its object blocks, the shorter
       // chunks keep the gathers in flight at once closer together (measured on
-      // one box: 10 M-entity KB step 2.369 -> 2.340 ms, training-shaped KB 9.05
+      // one card: 10 M-entity KB step 2.369 -> 2.340 ms, training-shaped KB 9.05
       // -> 9.00 ms), for twice the partial slots.  64 with object classes, where
       // one XCD's window of dY is what its L2 may hold: training-shaped KB dR
       // with its combine 2.92 -> 2.82 ms (subject classes, 10 M-entity KB:

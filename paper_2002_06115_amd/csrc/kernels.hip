@@ -19,9 +19,11 @@
 // needs no cross-lane reduction at all: every lane accumulates its own
 // columns and writes them when the row ends.  A row that crosses a chunk
 // boundary writes one double partial per chunk to a workspace slot and the
-// combine kernel adds them up in chunk order.  No atomics anywhere: every
-// output element is written by exactly one lane, with a fixed summation
-// order, so results are bitwise reproducible.
+// combine kernel adds them up in a fixed order.  No atomics anywhere: every
+// output element is written by one lane (by two, with the same bits, in the
+// last lanes of rows that are not a multiple of 4 floats), with a fixed
+// summation order, so results are bitwise reproducible.  Rows of at most 4
+// floats have a kernel of their own (narrow_kernel).
 //
 // Arithmetic: each product w * a * b is formed in double (the product of two
 // floats is exact in double) and accumulated in double; the float output is
