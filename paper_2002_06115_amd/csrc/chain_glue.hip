@@ -14,7 +14,7 @@
 // Short columns (one launch): the workgroup reduces its columns over all rows
 // and writes them.  Bound by latency (dependent passes over a few hundred KB),
 // so tiles are 4 columns wide where that gives more workgroups: 1000 rows of
-// 256 columns, L1 normalisation 10.2 -> 7.6 us, cross-entropy 27.2 -> 12.7
+// 256 columns, L1 normalisation 10.2 -> 7.3 us, cross-entropy 27.2 -> 12.1
 // (with 16-column tiles, a barrier per tree level and four passes before).
 //
 // Long columns (two launches, with the caller's scratch): the rows are cut
@@ -363,9 +363,10 @@ kbc_status launched() { return hipGetLastError() == hipSuccess ? KBC_OK : KBC_EH
 
 // -- how a call is launched -----------------------------------------------------------
 
-// Rows from which two launches win over one: each launch costs 3 to 4 us, and a
-// workgroup of the one-launch path takes 2.5 us per 1000 rows of its tile.
-constexpr int64_t kLongRows = 4096;
+// Rows from which two launches win over one: 2000 rows of 93 columns take the
+// one-launch path 6 to 8 us (softmax 11, cross-entropy 15), 4000 rows of 128 10 to
+// 27 (17, 35) against 7 (12, 15) in two launches.
+constexpr int64_t kLongRows = 2048;
 // Ranges of the two-launch path: about two workgroups per CU over all tiles, and
 // at least two rounds of kDepth rows per thread.
 constexpr int kMaxRanges = 512;
@@ -425,11 +426,13 @@ kbc_status launch(Args a, double *scratch, hipStream_t s) {
   }
   auto grid = [&](int tw) { return dim3((unsigned)(((int64_t)a.b + tw - 1) / tw)); };
   // 4-column tiles read 16 of a line's 128 bytes per row: right while the
-  // arrays are small and the chip is not full with 16-column ones.
+  // arrays are small and the chip is not full with 16-column ones (300 to 2000
+  // rows of 10 to 256 columns: 8-column tiles and 1024 threads are 5 to 40 %
+  // slower, 2-column tiles from 5 % faster to 30 % slower).
   if (a.b >= 4096 || a.n > kLongRows)
     hipLaunchKernelGGL((column_kernel<OP, 16, 1024>), grid(16), dim3(1024), 0, s, a);
   else if (a.n > 128)
-    hipLaunchKernelGGL((column_kernel<OP, 4, 1024>), grid(4), dim3(1024), 0, s, a);
+    hipLaunchKernelGGL((column_kernel<OP, 4, 512>), grid(4), dim3(512), 0, s, a);
   else
     hipLaunchKernelGGL((column_kernel<OP, 4, 256>), grid(4), dim3(256), 0, s, a);
   return launched();

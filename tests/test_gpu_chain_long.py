@@ -32,7 +32,7 @@ def host(t):
 
 # The last rows of the one-launch path and the first of the other; a last range
 # of one row; every tile width; columns beyond one tile.
-SHAPES = [(128, 5), (129, 4), (4096, 6), (4097, 1), (4097, 33), (5000, 2), (20_011, 3), (9001, 7),
+SHAPES = [(128, 5), (129, 4), (2048, 6), (2049, 5), (4097, 1), (4097, 33), (5000, 2), (20_011, 3), (9001, 7),
           (12_345, 16), (43_000, 93), (8193, 128), (70_001, 17), (4099, 300)]
 
 
