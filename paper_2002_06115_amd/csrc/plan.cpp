@@ -342,19 +342,16 @@ static void add_empty(PlanHost &P, int64_t first, int64_t count) {
     P.empty.push_back({(int32_t)q, (int32_t)std::min<int64_t>(kEmptyPiece, first + count - q)});
 }
 
-// Classes of the gathered ids, about equal in the number of triples that
-// gather each: the others than the heaviest cut into n_xcd consecutive ranges
-// of equal weight, then the heaviest one by one onto the lightest class.  One
-// XCD's gathers then stay within an eighth of the table's pages (and rows that
-// are near each other in a KB with local ids meet in one L2): against ids
+// Classes of the ids below n_ids, about equal in the number of triples of `col`
+// with each: the others than the heaviest cut into n_xcd consecutive ranges
+// of equal weight, then the heaviest one by one onto the lightest class.  The
+// other ids that one XCD gathers by are then neighbours in the table (and rows
+// that are near each other in a KB with local ids meet in one L2): against ids
 // modulo n_xcd, stream kernels forward / dX / dR, us: 10 M entities, b = 32, 705
 // / 792 / 1469 -> 650 / 731 / 1431; 2 M entities, b = 256, 2036 / 2981 / 2944 ->
 // 2030 / 2811 / 2841; grid of 10^6 cells, b = 128, 363 / 363 / 549 -> 336 / 336 /
-// 427.  Empty when the id space is far larger than the KB (then the class of id
-// a is its range of the id space).
+// 427.
 static std::vector<uint8_t> id_classes(const std::vector<int32_t> &col, int64_t n_ids, int X) {
-  const int64_t n_t = (int64_t)col.size();
-  if (X <= 1 || n_ids <= 0 || n_ids > 4 * n_t + (int64_t(1) << 20)) return {};
   std::vector<int32_t> cnt(n_ids, 0);
   for (int32_t a : col) ++cnt[a];
   std::vector<uint8_t> cls(n_ids);
@@ -397,6 +394,27 @@ static std::vector<uint8_t> id_classes(const std::vector<int32_t> &col, int64_t 
     load[best] += cnt[h];
   }
   return cls;
+}
+
+// Ids in place of `col`'s that number the ids that occur, in their order, from 0;
+// returns how many there are.  For id spaces far larger than the KB, where
+// neither a table over the space nor ranges of it (which need not hold equal
+// numbers of triples) would do.
+static int64_t compact_ids(std::vector<int32_t> &col, int threads) {
+  const int64_t n = (int64_t)col.size();
+  std::vector<uint64_t> key(n);
+  std::vector<int32_t> at(n);
+  for (int64_t l = 0; l < n; ++l) {
+    key[l] = (uint64_t)col[l];
+    at[l] = (int32_t)l;
+  }
+  radix_sort(key, &at, threads);
+  int64_t ids = 0;
+  for (int64_t i = 0; i < n; ++i) {
+    ids += i == 0 || key[i] != key[i - 1];
+    col[at[i]] = (int32_t)(ids - 1);
+  }
+  return ids;
 }
 
 double hub_share(const std::vector<int32_t> &row, int64_t hub_min) {
@@ -460,15 +478,22 @@ PlanHost plan_layout(const LayoutHost &L, const PlanOptions &opt) {
   // inside hub rows of a plan with several lists.
   std::vector<int32_t> pos(n_t);
   for (int64_t i = 0; i < n_t; ++i) pos[i] = (int32_t)i;
-  const std::vector<int32_t> &cls_col = opt.class_by_b ? L.col_b : L.col_a;
-  const int64_t cls_ids = opt.class_by_b ? opt.n_ids_b : opt.n_ids_a;
-  const std::vector<uint8_t> cls_tab = id_classes(cls_col, cls_ids, X);
+  // Classes by id, or, where the id space is far larger than the KB, by the id's
+  // rank among those that occur.
+  const std::vector<int32_t> &id_col = opt.class_by_b ? L.col_b : L.col_a;
+  int64_t cls_ids = opt.class_by_b ? opt.n_ids_b : opt.n_ids_a;
+  std::vector<int32_t> ranks;
+  std::vector<uint8_t> cls_tab;
+  if (X > 1 && n_t > 0) {
+    if (cls_ids <= 0 || cls_ids > 4 * n_t + (int64_t(1) << 20)) {
+      ranks = id_col;
+      cls_ids = compact_ids(ranks, std::max(1, host_threads() / 3));
+    }
+    cls_tab = id_classes(ranks.empty() ? id_col : ranks, cls_ids, X);
+  }
+  const std::vector<int32_t> &cls_col = ranks.empty() ? id_col : ranks;
   // The class of the triple at position l.
-  auto cls_at = [&](int64_t l) -> int {
-    const int32_t id = cls_col[l];
-    if (!cls_tab.empty()) return (int)cls_tab[id];
-    return (int)std::min<int64_t>(X - 1, (int64_t)id * X / std::max<int64_t>(1, cls_ids));
-  };
+  auto cls_at = [&](int64_t l) -> int { return (int)cls_tab[cls_col[l]]; };
 
   // Segments per list: a hub row's class segments first (rows in order),
   // then whole rows.  `alone`: the segment is its row's only one.
