@@ -1110,8 +1110,10 @@ template <int LANE, bool BUF, bool WT, bool RES, bool LDSB>
 const void *stream_fn(int lpt) {
   switch (lpt) {
     case 1:
-      if constexpr (LANE == kRaggedLane)
-        return nullptr;  // at least two lanes
+      // (One lane per group of a row of 5 floats or more: KBFOLLOW_MAX_LPT=1,
+      // which does not narrow the LDS variant's groups.)
+      if constexpr (LANE == kRaggedLane && LDSB)
+        return nullptr;
       else
         return reinterpret_cast<const void *>(&stream_kernel<LANE, 1, BUF, WT, RES, LDSB>);
     case 2: return reinterpret_cast<const void *>(&stream_kernel<LANE, 2, BUF, WT, RES, LDSB>);

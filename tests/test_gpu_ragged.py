@@ -71,6 +71,35 @@ def test_ragged_widths(kbf, b, weighted, path, monkeypatch):
         assert np.array_equal(a, c), (name, b, weighted, path)
 
 
+# Every cap on the lanes of a group, one lane included, at the narrowest row, a
+# last lane of each kind, several slices, on both load paths.
+@pytest.mark.parametrize("b", [5, 6, 7, 10, 33])
+@pytest.mark.parametrize("max_lpt", ["1", "2", "4"])
+@pytest.mark.parametrize("weighted,plain", [(False, "0"), (False, "1"), (True, "0"), (True, "1")])
+def test_narrower_lane_groups(kbf, b, max_lpt, weighted, plain, monkeypatch):
+    monkeypatch.setenv("KBFOLLOW_CHUNK", "16")
+    monkeypatch.setenv("KBFOLLOW_REL_CHUNK", "16")
+    monkeypatch.setenv("KBFOLLOW_B_IN_LDS", "0")
+    monkeypatch.setenv("KBFOLLOW_PLAIN_LOADS", plain)
+    g = np.random.default_rng(b)
+    n_e, n_r, n_t = 300, 7, 5000
+    s, r, o = (g.integers(0, n, n_t).astype(np.int32) for n in (n_e, n_r, n_e - 40))
+    w = g.uniform(0.1, 2.0, n_t).astype(np.float32) if weighted else None
+    X, R, dY, Z = (g.standard_normal((b, n)).astype(np.float32) for n in (n_e, n_r, n_e, n_e))
+    dev = [to_em(a) for a in (X, R, dY, Z)]
+    want = outputs(kbf, [s, r, o], n_e, n_r, *dev, w)
+    assert_close(want[0], oracle.follow(s, r, o, n_e, n_r, X, R, weight=w), "Y")
+    monkeypatch.setenv("KBFOLLOW_MAX_LPT", max_lpt)
+    kb = kbf.KB(s, r, o, n_e, n_r, weight=w)
+    kernel = kb.phase_kernels(b)["fwd_stream"]
+    kb.close()
+    assert kernel.startswith(f"stream_kernel<-4, {max_lpt}," if b > 4 * int(max_lpt) else
+                             "stream_kernel<-4, "), kernel
+    got = outputs(kbf, [s, r, o], n_e, n_r, *dev, w)
+    for i, (a, c) in enumerate(zip(got, want)):
+        assert np.array_equal(a, c), (i, b, max_lpt)
+
+
 # The narrow kernel (a lane per entry): every width, chunks of one, several and
 # many steps, B in LDS (few relations) and not (1500 relations at b = 4; X in dR).
 @pytest.mark.parametrize("b", [1, 2, 3, 4])
