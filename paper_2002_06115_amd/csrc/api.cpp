@@ -458,25 +458,6 @@ kb_status kb_create(int64_t n_entities, int64_t n_relations, int64_t n_triples,
     kb->n_relations = n_relations;
     kb->n_triples = n_triples;
     kb->weighted = weight != nullptr;
-    // Chunk length: 256 entries, shorter for small streams so that there are
-    // at least ~32 K chunks to spread over the GPU (never below 16).
-    auto default_chunk = [](int64_t entries) {
-      int32_t c = 256;
-      while (c > 16 && entries / c < 32768) c /= 2;
-      return c;
-    };
-    // Down to 32 entries for 96 K chunks where at most an eighth of the triples
-    // lie in hub rows, so that shorter chunks add few partials: the rows in
-    // flight at once are then closer together, and so are what they gather in a
-    // KB with local ids (grid of 10^6 cells, b = 128, 128 -> 32 entries: 336 ->
-    // 297 us; 2 M entities and 20 M triples with uniform subjects per object, b =
-    // 1, 256 -> 128: 107 -> 105).  With hubs the partials cost more than it gives
-    // (10 M entities, b = 32, 256 -> 128: forward 786 -> 809).
-    auto entity_chunk = [&](int64_t entries, double hubs) {
-      int32_t c = default_chunk(entries);
-      while (hubs <= 0.125 && c > 32 && entries / c < 98304) c /= 2;
-      return c;
-    };
     // A chunk is a whole number of kernel steps.
     auto whole_steps = [](int32_t c) {
       return std::max(kChunkQuantum, (c + kChunkQuantum - 1) / kChunkQuantum * kChunkQuantum);
@@ -502,10 +483,8 @@ kb_status kb_create(int64_t n_entities, int64_t n_relations, int64_t n_triples,
       // which keeps runs of equal subject, whose X row is read once per run.
       const int32_t n_xcd = std::max(1, std::min(kMaxXcd, env_int("KBFOLLOW_XCD", 8)));
       const int64_t hub_min = std::max(1, env_int("KBFOLLOW_HUB_MIN", 256));
-      const int64_t ent = n_triples + n_entities;
       auto chunk_of = [&](int k) {
-        return whole_steps(
-            env_int("KBFOLLOW_CHUNK", entity_chunk(ent, hub_share(H[k].row, hub_min))));
+        return whole_steps(env_int("KBFOLLOW_CHUNK", entity_chunk(H[k], n_entities)));
       };
       const bool band = env_int("KBFOLLOW_BAND", 1) != 0;
       // dR's lists are classed by subject (the X row read once per run) when

@@ -417,14 +417,57 @@ static int64_t compact_ids(std::vector<int32_t> &col, int threads) {
   return ids;
 }
 
-double hub_share(const std::vector<int32_t> &row, int64_t hub_min) {
+double hub_share(const std::vector<int32_t> &row, int64_t len) {
   int64_t in_hubs = 0;
   const int64_t n = (int64_t)row.size();
   for (int64_t beg = 0, end; beg < n; beg = end) {
     for (end = beg + 1; end < n && row[end] == row[beg];) ++end;
-    if (end - beg >= hub_min) in_hubs += end - beg;
+    if (end - beg >= len) in_hubs += end - beg;
   }
   return n ? (double)in_hubs / (double)n : 0.0;
+}
+
+bool local_ids(const LayoutHost &L) {
+  constexpr int64_t kSamples = 4096;
+  const int64_t n = (int64_t)L.row.size();
+  if (n == 0) return false;
+  // The middle triple of the row at position p, and the row after it.
+  auto middle = [&](int64_t p, int64_t *next) {
+    const auto r = std::equal_range(L.row.begin(), L.row.end(), L.row[p]);
+    *next = r.second - L.row.begin();
+    return (int64_t)L.col_a[(r.first - L.row.begin()) + (r.second - r.first) / 2];
+  };
+  std::vector<int64_t> near, far;
+  for (int64_t i = 0; i < kSamples; ++i) {
+    int64_t next, other, skip;
+    const int64_t id = middle(i * n / kSamples, &next);
+    if (next >= n) break;
+    other = middle((i + kSamples / 2) % kSamples * n / kSamples, &skip);
+    far.push_back(std::abs(other - id));
+    near.push_back(std::abs(middle(next, &skip) - id));
+  }
+  if (near.size() < kSamples / 2) return false;
+  auto median = [](std::vector<int64_t> &v) {
+    std::nth_element(v.begin(), v.begin() + (std::ptrdiff_t)(v.size() / 2), v.end());
+    return v[v.size() / 2];
+  };
+  // (Neighbours that gather one and the same id are alike, not near.)
+  const int64_t m = median(near);
+  return m > 0 && m <= median(far) / 16;
+}
+
+int32_t default_chunk(int64_t entries) {
+  int32_t c = 256;
+  while (c > 16 && entries / c < 32768) c /= 2;
+  return c;
+}
+
+int32_t entity_chunk(const LayoutHost &L, int64_t n_entities) {
+  const int64_t entries = (int64_t)L.row.size() + n_entities;
+  int32_t c = default_chunk(entries);
+  if (c <= 32 || entries / c >= 98304 || !local_ids(L)) return c;
+  while (c > 32 && entries / c < 98304 && hub_share(L.row, c / 16 + 1) <= 0.125) c /= 2;
+  return c;
 }
 
 double top_id_share(const std::vector<int32_t> &col, int64_t n_ids, double frac) {

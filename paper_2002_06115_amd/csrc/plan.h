@@ -142,8 +142,32 @@ struct PlanHost {
 // ceil(frac * n_ids) most frequent ones: how skewed the id distribution is.
 double top_id_share(const std::vector<int32_t> &col, int64_t n_ids, double frac);
 
-// The share of a sorted layout's triples that lie in rows of at least hub_min.
-double hub_share(const std::vector<int32_t> &row, int64_t hub_min);
+// The share of a sorted layout's triples that lie in rows of at least `len`.
+double hub_share(const std::vector<int32_t> &row, int64_t len);
+
+// Whether the rows of a layout that follow each other gather from places that
+// are near each other (a grid, a band matrix): half of the sampled pairs of
+// neighbouring rows are closer, by the id that their middle triples gather, than
+// a sixteenth of what half of the pairs of rows far apart are.
+bool local_ids(const LayoutHost &layout);
+
+// Chunk length of a stream of `entries`: 256, shorter for small ones so that
+// there are at least ~32 K chunks to spread over the GPU (never below 16).
+int32_t default_chunk(int64_t entries);
+
+// Chunk length of the forward or dX layout over n_entities rows: the default, or
+// down to 32 entries for 96 K chunks where the gathered ids are local and at most
+// an eighth of the triples lie in rows longer than an eighth of the shorter chunk
+// (up to that length a row that does not fit in what is left of a chunk leaves it
+// to no-op markers, so packing splits none).  The rows in flight at once are then closer together, and
+// so is what they gather: grid of 10^6 cells, b = 128, 128 -> 32 entries: 336 ->
+// 300 us (b = 64: 170 -> 162, b = 10: 74 -> 62, b = 32: 77 -> 82).  With ids
+// spread evenly there is nothing to bring together, and the starts of more
+// chunks cost: 500 k entities with 10 triples each, b = 32, 128 -> 32 entries:
+// 114 -> 127 us; 300 k with 30 each, b = 32, 256 -> 64: 175 -> 191.  Rows longer
+// than a chunk add partials to that: 100 k entities with 80 triples each, b = 32,
+// 128 -> 64: 127 -> 148, and 67 k -> 220 k slots.
+int32_t entity_chunk(const LayoutHost &layout, int64_t n_entities);
 
 // Returns "" when the triple arrays are valid, else a message; *range_error
 // tells an out-of-range id (KB_ERANGE) from any other problem (KB_EINVAL).
