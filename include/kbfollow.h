@@ -129,8 +129,9 @@ typedef enum {
  *                                       subject id held per run (1); default:
  *                                       by subject when the top 1 % of
  *                                       objects hold a quarter of the triples;
- *   KBFOLLOW_DR_BLOCKS                  blocks of the object id leading
- *                                       dR's hub segments (64; 0 or 1: none);
+ *   KBFOLLOW_DR_BLOCKS                  blocks of the object id (of each class
+ *                                       of objects) leading dR's hub segments
+ *                                       (64; 0 or 1: none);
  *   KBFOLLOW_MAX_LPT                    widest lane group of the register
  *                                       variant, every pass (default: 32, 8
  *                                       for dR from b = 128; bitwise the

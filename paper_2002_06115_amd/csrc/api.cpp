@@ -504,19 +504,21 @@ kb_status kb_create(int64_t n_entities, int64_t n_relations, int64_t n_triples,
       const bool dr_class_b = cls_env >= 0
                                   ? cls_env != 0
                                   : top_id_share(H[BY_REL].col_a, n_entities, 0.01) >= 0.25;
-      // dR's hub segments led by 64 blocks of the object id, so that the
-      // chunks in flight at once gather dY from a few blocks: dR 0.815 ->
-      // 0.79 ms on the 10 M-entity KB with the passes serial (8 to 32 blocks
-      // the same within 1 %); on the training-shaped KB 3.35 -> 3.04 ms with
-      // object classes (16 -> 64 blocks).
+      // dR's hub segments led by 64 blocks of the object id (64 to a class of
+      // objects, see PlanOptions::a_blocks), so that the chunks in flight at
+      // once gather dY from a few blocks: dR 0.815 -> 0.79 ms on the 10
+      // M-entity KB with the passes serial (8 to 32 blocks the same within
+      // 1 %); on the training-shaped KB, against no blocks, 3.35 -> 2.66 ms.
       const int32_t dr_blocks = env_int("KBFOLLOW_DR_BLOCKS", 64);
       // dR's chunks at most 128 entries: with its object blocks, the shorter
       // chunks keep the gathers in flight at once closer together (measured on
       // one card: 10 M-entity KB step 2.369 -> 2.340 ms, training-shaped KB 9.05
       // -> 9.00 ms), for twice the partial slots.  64 with object classes, where
-      // one XCD's window of dY is what its L2 may hold: training-shaped KB dR
-      // with its combine 2.92 -> 2.82 ms (subject classes, 10 M-entity KB:
-      // backward 1.478 -> 1.505, not taken).
+      // one XCD's window of dY is what its L2 may hold, against 128: 500 k
+      // entities, 5 M triples, 50 relations, b = 32 / 64 / 256: 147 / 288 / 1208
+      // -> 137 / 262 / 1078 us; the training-shaped KB, whose windows are few
+      // already, 331 / 614 / 2577 -> 338 / 641 / 2659 (subject classes, 10
+      // M-entity KB: backward 1.478 -> 1.505, not taken).
       const int32_t chunk_rel = whole_steps(
           env_int("KBFOLLOW_REL_CHUNK", std::min<int32_t>(dr_class_b ? 128 : 64,
                                                           default_chunk(n_triples + n_relations))));

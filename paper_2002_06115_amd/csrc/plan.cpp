@@ -554,8 +554,10 @@ PlanHost plan_layout(const LayoutHost &L, const PlanOptions &opt) {
     std::vector<int32_t> idx;
     std::vector<std::pair<uint64_t, int32_t>> kp;
     const int sort_threads = std::max(1, host_threads() / 3);
+    // (Classes of the gathered ids are ranges of them: a_blocks blocks in each.)
     const int32_t a_blocks =
-        opt.hub_by_a ? 0 : std::max<int32_t>(0, std::min<int32_t>(opt.a_blocks, 64));
+        (opt.hub_by_a ? 0 : std::max<int32_t>(0, std::min<int32_t>(opt.a_blocks, 64))) *
+        (opt.class_by_b ? 1 : X);
     std::vector<const RowSpan *> small;
     int64_t total = 0;
     for (const RowSpan &r : rows) {
@@ -578,18 +580,19 @@ PlanHost plan_layout(const LayoutHost &L, const PlanOptions &opt) {
       while (bx < 63 && (mx >> bx) != 0) ++bx;
       while (by < 63 && (my >> by) != 0) ++by;
       // Blocks of the gathered id ahead of the second operand (3 bits of
-      // class, at most 6 of block).
+      // class, at most 9 of block, as many as the key has left).
       int bk = 0;
       if (a_blocks > 1) {
         while ((1 << bk) < a_blocks) ++bk;
-        if (3 + bk + bx + by > 64) bk = 0;
+        bk = std::max(0, std::min(bk, 64 - 3 - bx - by));
       }
+      const int64_t n_blocks = std::min<int64_t>(a_blocks, int64_t(1) << bk);
       auto key_of = [&](int64_t l) {
         const uint64_t c = (uint64_t)cls_at(l);
         const uint64_t x = (uint64_t)(opt.hub_by_a ? L.col_a[l] : L.col_b[l]);
         const uint64_t y = (uint64_t)(opt.hub_by_a ? L.col_b[l] : L.col_a[l]);
         const uint64_t k =
-            bk ? (uint64_t)((int64_t)L.col_a[l] * a_blocks / std::max<int64_t>(1, opt.n_ids_a))
+            bk ? (uint64_t)((int64_t)L.col_a[l] * n_blocks / std::max<int64_t>(1, opt.n_ids_a))
                : 0;
         return (c << (bk + bx + by)) | (k << (bx + by)) | (x << by) | y;
       };

@@ -104,9 +104,12 @@ struct PlanOptions {
   bool class_by_b = false;
   int64_t n_ids_b = 0;     // size of the second operand's id space
   // With hub_by_a false: hub segments ordered by (block of the gathered id,
-  // second operand, gathered id), the gathered ids cut into a_blocks equal
-  // ranges (0 or 1: no blocks), so that with band the chunks of a list walk
-  // the gathered table one block at a time.
+  // second operand, gathered id), so that with band the chunks of a list walk
+  // the gathered table one block at a time (0 or 1: no blocks): the ids cut
+  // into a_blocks equal ranges, or, where the classes are ranges of them (not
+  // class_by_b), a_blocks to each class.  (Against a_blocks over all classes, 64:
+  // 2 M entities, 20 M triples, 1000 relations, dR at b = 64 / 128 / 256: 794 /
+  // 1391 / 2816 -> 640 / 1314 / 2658 us; 16 to a class 718 / 1326 / 2692.)
   int32_t a_blocks = 0;
   // Above fan_in: rows (and levels) of more than fan_in partials are combined by
   // wide tasks of up to this many, a workgroup each (0: none).

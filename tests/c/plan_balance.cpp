@@ -1,9 +1,11 @@
 // How evenly a plan spreads its chunks over the XCD lists, for KBs whose ids are
 // a small part of the id space: clustered at its start, spread over it, with and
 // without hot ids.  Prints one line per case; exit status 0 when the longest list
-// of every layout is within a tenth of the shortest (or a few chunks).  Built and
+// of every layout is within a tenth of the shortest (or a few chunks), and dR's
+// chunks gather from as few blocks of the table as its options ask for.  Built and
 // run by tests/test_plan_balance.py.
 #define main plan_sanitized_main
+#include <algorithm>
 #include "plan_sanitized.cpp"
 #undef main
 
@@ -51,6 +53,44 @@ static void balance_case(const char *what, int64_t n_e, int64_t used, int64_t n_
     }
 }
 
+// dR with classes of the gathered ids: half of the chunks (more than half of the
+// triples are not among the heaviest ids, which any list may hold) stay within
+// two of the a_blocks blocks of a class's range of the ids.
+static void window_case() {
+  const int64_t n_e = 400'000, n_r = 10, n_t = 800'000;
+  std::mt19937_64 g(23);
+  std::vector<int32_t> s(n_t), r(n_t), o(n_t);
+  for (int64_t l = 0; l < n_t; ++l)
+    s[l] = (int32_t)(g() % n_e), r[l] = (int32_t)(g() % n_r), o[l] = (int32_t)(g() % n_e);
+  LayoutHost L[3];
+  build_layouts(n_e, n_r, n_t, s.data(), r.data(), o.data(), nullptr, false, false, L);
+  for (int32_t blocks : {16, 64}) {
+    PlanOptions po;
+    po.chunk = 64;
+    po.n_xcd = 8;
+    po.hub_by_a = false;
+    po.n_ids_a = po.n_ids_b = n_e;
+    po.a_blocks = blocks;
+    po.pack = true;
+    const PlanHost P = plan_layout(L[2], po);
+    std::vector<int64_t> span;
+    for (int64_t c = 0; c < P.n_chunks; ++c) {
+      int32_t lo = INT32_MAX, hi = -1;
+      for (int64_t p = c * po.chunk; p < (c + 1) * po.chunk; ++p)
+        if (P.entries[p].x >= 0) {
+          lo = std::min(lo, P.entries[p].x & kIdMask);
+          hi = std::max(hi, P.entries[p].x & kIdMask);
+        }
+      if (hi >= 0) span.push_back(hi - lo);
+    }
+    std::nth_element(span.begin(), span.begin() + (std::ptrdiff_t)(span.size() / 2), span.end());
+    const int64_t median = span[span.size() / 2], most = 2 * n_e / po.n_xcd / blocks;
+    std::printf("%d blocks: chunks gather from %lld ids (median)\n", blocks, (long long)median);
+    CHECK(median <= most, "%d blocks: chunks over %lld ids, at most %lld", blocks,
+          (long long)median, (long long)most);
+  }
+}
+
 int main() {
   // Above 4 ids per triple and 2^20 more: the id space counts as sparse.
   const int64_t n_e = 4'000'000, n_t = 300'000;
@@ -61,6 +101,7 @@ int main() {
   // The same ids in a space of their own size: the dense path.
   balance_case("dense", n_e / 10, n_e / 10, n_t, 0);
   balance_case("dense, hot ids", n_e / 10, n_e / 10, n_t, 20);
+  window_case();
   if (failures) {
     std::fprintf(stderr, "%d checks failed\n", failures);
     return 1;
