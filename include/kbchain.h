@@ -22,7 +22,7 @@
  * Streams and memory: every call only enqueues work on `stream` (hipStream_t,
  * NULL = null stream), allocates nothing and returns.  All pointers are
  * DEVICE pointers; input and output arrays must not overlap unless stated.
- * A workgroup reduces 4 or 16 columns over all n rows.  Columns of more than a
+ * A workgroup reduces 4, 8 or 16 columns over all n rows.  Columns of more than a
  * few thousand rows are better cut into ranges of rows, whose partial values
  * need device scratch: the *_scratch forms take it (kbc_scratch_size bytes, 8-byte
  * aligned, used by that call alone until it has run), and are the plain forms

@@ -13,8 +13,8 @@
 //
 // Short columns (one launch): the workgroup reduces its columns over all rows
 // and writes them.  Bound by latency (dependent passes over a few hundred KB),
-// so tiles are 4 columns wide where that gives more workgroups: 1000 rows of
-// 256 columns, L1 normalisation 10.2 -> 7.3 us, cross-entropy 27.2 -> 12.1
+// so tiles are 4 columns wide where that gives more workgroups (see launch): 1000
+// rows of 256 columns, L1 normalisation 10.2 -> 7.3 us, cross-entropy 27.2 -> 12.1
 // (with 16-column tiles, a barrier per tree level and four passes before).
 //
 // Long columns (two launches, with the caller's scratch): the rows are cut
@@ -46,9 +46,10 @@ struct Span {
 };
 
 template <int TW, int THREADS>
-__device__ __forceinline__ Span span(int64_t r0, int64_t r1, int32_t b) {
+__device__ __forceinline__ Span span(int64_t r0, int64_t r1, int32_t b, int64_t tile) {
   Span s;
-  s.col = (int)(blockIdx.x * TW + threadIdx.x % TW);
+  const int64_t col = tile * TW + threadIdx.x % TW;
+  s.col = col < b ? (int)col : b;
   s.begin = r0 + (int64_t)(threadIdx.x / TW);
   s.end = r1;
   s.step = THREADS / TW;
@@ -278,11 +279,16 @@ __device__ __forceinline__ void apply(const Args &a, const Span &s, const Stats 
   }
 }
 
-// One launch: all rows of TW columns.
+// One launch: all rows of TW columns.  Tiles that share cache lines are on one
+// XCD (workgroup w runs on XCD w mod 8; the grid is a multiple of 8): in order,
+// every XCD's L2 fetched every line, which cost wide arrays up to 3.5 times the
+// time (1000 rows of 2048 columns, 4-column tiles, softmax backward 46 -> 12 us).
+constexpr int kXcds = 8;
 template <int OP, int TW, int THREADS>
 __global__ __launch_bounds__(THREADS) void column_kernel(Args a) {
   __shared__ double lds[3 * (THREADS / 64) * TW];
-  const Span s = span<TW, THREADS>(0, a.n, a.b);
+  const Span s = span<TW, THREADS>(
+      0, a.n, a.b, (int64_t)(blockIdx.x % kXcds) * (gridDim.x / kXcds) + blockIdx.x / kXcds);
   const Stats r = reduce_combine<OP, TW, THREADS>(reduce_part<OP>(a, s), lds);
   apply<OP>(a, s, r, s.valid && threadIdx.x < TW);
 }
@@ -293,7 +299,7 @@ template <int OP, int TW>
 __global__ __launch_bounds__(kLongThreads) void range_kernel(Args a) {
   __shared__ double lds[3 * (kLongThreads / 64) * TW];
   const int64_t r0 = (int64_t)blockIdx.y * a.rows_per;
-  const Span s = span<TW, kLongThreads>(r0, min(a.n, r0 + a.rows_per), a.b);
+  const Span s = span<TW, kLongThreads>(r0, min(a.n, r0 + a.rows_per), a.b, blockIdx.x);
   const Stats r = reduce_combine<OP, TW, kLongThreads>(reduce_part<OP>(a, s), lds);
   if (!(s.col < a.b) || threadIdx.x >= TW) return;
   double *p = a.part + (int64_t)blockIdx.y * a.b + s.col;
@@ -310,7 +316,7 @@ template <int OP, int TW>
 __global__ __launch_bounds__(kLongThreads) void apply_kernel(Args a) {
   __shared__ double lds[3 * (kLongThreads / 64) * TW];
   const int64_t r0 = (int64_t)blockIdx.y * a.rows_per;
-  const Span s = span<TW, kLongThreads>(r0, min(a.n, r0 + a.rows_per), a.b);
+  const Span s = span<TW, kLongThreads>(r0, min(a.n, r0 + a.rows_per), a.b, blockIdx.x);
   constexpr int kPhases = kLongThreads / TW;
   const int64_t plane = (int64_t)a.ranges * a.b;
   Stats p = {OP == kSoftmax || OP == kXent ? -INFINITY : 0.0, 0.0, 0.0, 0.0};
@@ -424,17 +430,31 @@ kbc_status launch(Args a, double *scratch, hipStream_t s) {
     }
     return launched();
   }
-  auto grid = [&](int tw) { return dim3((unsigned)(((int64_t)a.b + tw - 1) / tw)); };
-  // 4-column tiles read 16 of a line's 128 bytes per row: right while the
-  // arrays are small and the chip is not full with 16-column ones (300 to 2000
-  // rows of 10 to 256 columns: 8-column tiles and 1024 threads are 5 to 40 %
-  // slower, 2-column tiles from 5 % faster to 30 % slower).
-  if (a.b >= 4096 || a.n > kLongRows)
-    hipLaunchKernelGGL((column_kernel<OP, 16, 1024>), grid(16), dim3(1024), 0, s, a);
-  else if (a.n > 128)
-    hipLaunchKernelGGL((column_kernel<OP, 4, 512>), grid(4), dim3(512), 0, s, a);
+  auto go = [&](auto kernel, int tw, int threads) {
+    const int64_t tiles = ((int64_t)a.b + tw - 1) / tw;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)((tiles + kXcds - 1) / kXcds * kXcds)), dim3(threads),
+                       0, s, a);
+  };
+  // Narrow tiles give a narrow array more workgroups, wide ones read more of each
+  // line.  The five operations together, us, with 4 / 8 / 16 columns (512, 512
+  // and 1024 threads): 1000 rows of 256 columns 33 / 41 / 59, of 768 42 / 47 / 65,
+  // of 1024 50 / 50 / 67, of 4000 138 / 112 / 105; 400 rows of 1024 34 / 35 / 45,
+  // of 4000 84 / 73 / 74.  Up to 128 rows give 512 threads too little to do (60 rows
+  // of 1024 columns, tiles of 8, 27 -> 25 with 256; of 8000, tiles of 16 and 1024
+  // threads, 103 -> 87).
+  const bool few = a.n <= 128;
+  if (a.n > kLongRows || (a.b >= 4096 && !few))
+    go(column_kernel<OP, 16, 1024>, 16, 1024);
+  else if (a.b >= 4096)
+    go(column_kernel<OP, 16, 256>, 16, 256);
+  else if (a.b >= 1024 && !few)
+    go(column_kernel<OP, 8, 512>, 8, 512);
+  else if (a.b >= 1024)
+    go(column_kernel<OP, 8, 256>, 8, 256);
+  else if (!few)
+    go(column_kernel<OP, 4, 512>, 4, 512);
   else
-    hipLaunchKernelGGL((column_kernel<OP, 4, 256>), grid(4), dim3(256), 0, s, a);
+    go(column_kernel<OP, 4, 256>, 4, 256);
   return launched();
 }
 

@@ -36,7 +36,13 @@ SHAPES = [(128, 5), (129, 4), (2048, 6), (2049, 5), (4097, 1), (4097, 33), (5000
           (12_345, 16), (43_000, 93), (8193, 128), (70_001, 17), (4099, 300)]
 
 
-@pytest.mark.parametrize("n,b", SHAPES)
+# Wide columns: the first and last widths of each tile of the one-launch path, on
+# both sides of 128 rows, with tiles that no XCD's share of the grid is full of.
+WIDE = [(3, 1023), (128, 1024), (129, 1024), (1000, 1025), (128, 4095), (200, 4095), (128, 4096),
+        (129, 4096), (60, 4100), (300, 5001)]
+
+
+@pytest.mark.parametrize("n,b", SHAPES + WIDE)
 def test_every_operation(chain, n, b):
     g = np.random.default_rng(n + b)
     z = (3 * g.standard_normal((n, b))).astype(np.float32)
