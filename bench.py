@@ -116,8 +116,8 @@ def mangled_name(short):
     name, args = m.group(1), [a.strip() for a in m.group(2).split(",")]
     enc = "".join(f"Lb{1 if a == 'true' else 0}E" if a in ("true", "false") else f"Li{a.replace('-', 'n')}E"
                   for a in args)
-    params = {"stream_kernel": "NS_10StreamArgsE", "tail_kernel": "NS_8TailArgsE",
-              "combine_kernel": "NS_8TailArgsE"}.get(name)
+    params = {"stream_kernel": "NS_10StreamArgsE", "narrow_kernel": "NS_10StreamArgsE",
+              "tail_kernel": "NS_8TailArgsE", "combine_kernel": "NS_8TailArgsE"}.get(name)
     if params is None:
         return None
     return f"_ZN3kbf12_GLOBAL__N_1{len(name)}{name}I{enc}EEv{params}"

@@ -328,7 +328,10 @@ kb_status kb_checked_violations(uint64_t *count, int32_t reset);
 /* Phases whose GPU time is recorded when profiling is on.  Per pass: STREAM
  * is the stream kernel; TAIL the one launch that does the first combine
  * level (rows split over several chunks) and writes the rows without
- * triples; COMBINE the further combine levels (rows split over many chunks). */
+ * triples; COMBINE the further combine levels (rows split over many chunks).
+ * Where the rows without triples are written by a sweep over the whole output
+ * before the stream kernel, TAIL is that launch and the first combine level's
+ * together, counted as one. */
 typedef enum {
   KB_PH_FWD_STREAM = 0, KB_PH_FWD_TAIL, KB_PH_FWD_COMBINE,
   KB_PH_DX_STREAM, KB_PH_DX_TAIL, KB_PH_DX_COMBINE,
@@ -358,7 +361,8 @@ kb_status kb_profile_read(kb_t *kb, double *ms, int64_t *launches);
 /* The kernel a phase launches for this KB at batch size b, as profilers
  * print it (e.g. "stream_kernel<4, 8, true, false, false, true>"), written
  * NUL-terminated into name[len] (truncated if longer); "" when the phase
- * launches nothing.  residual != 0 describes kb_follow_residual and
+ * launches nothing, "fill_kernel<false> + tail_kernel<...>" for a TAIL phase of
+ * two launches.  residual != 0 describes kb_follow_residual and
  * kb_follow_backward_residual instead of kb_follow and kb_follow_backward.
  * Uses the runtime's occupancy calculator on the KB's device (which must be
  * current) but enqueues nothing.  KB_EINVAL for a NULL kb or name, len = 0,

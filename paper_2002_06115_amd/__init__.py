@@ -339,7 +339,8 @@ class KB:
 
     def phase_kernels(self, b, residual=False):
         """{phase: the kernel it launches at batch size b, as profilers print
-        it ("" when the phase launches nothing)}."""
+        it ("" when the phase launches nothing, both joined by " + " where a
+        tail phase sweeps the output first)}."""
         out = {}
         buf = ctypes.create_string_buffer(256)
         for i, p in enumerate(PHASES):

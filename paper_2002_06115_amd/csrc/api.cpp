@@ -63,6 +63,7 @@ struct Timing {
   struct Rec {
     int phase;
     hipEvent_t start, stop;
+    bool counts;  // false: time of a launch that another record of the phase counts
   };
   std::vector<Rec> recs;
 };
@@ -199,6 +200,7 @@ struct PhaseScope {
   // otherwise the events go to the scope's one kernel launch, which sets
   // them (see launch_stream), and the scope only files them.
   bool record_events = true;
+  bool counts = true;  // see Timing::Rec
   PhaseScope(const kb_t *k, int ph, hipStream_t st, bool record = true)
       : kb(k), phase(ph), s(st), record_events(record) {
     if (!((kb->timing.mask >> phase) & 1u)) return;
@@ -212,7 +214,7 @@ struct PhaseScope {
   ~PhaseScope() {
     if (start && stop) {
       if (record_events) (void)hipEventRecord(stop, s);
-      kb->timing.recs.push_back({phase, start, stop});
+      kb->timing.recs.push_back({phase, start, stop, counts});
       return;
     }
     // Only one event could be created: keep it for later, record nothing.
@@ -286,6 +288,7 @@ kb_status run_pass(const kb_t *kb, const DevLayout &D, int ph_base, const float 
   const bool prefill = Z != out && prefill_rows(kb, D, b, Z != nullptr);
   if (prefill) {
     PhaseScope scope(kb, ph_base + 1, s);
+    scope.counts = false;  // the tail's bracket below counts for both
     hipError_t e = launch_fill(out, D.rows * (int64_t)b, res, gamma, s);
     if (e != hipSuccess) return hip_fail(e, "fill kernel launch");
   }
@@ -819,9 +822,11 @@ kb_status kb_phase_kernel(const kb_t *kb, int32_t b, int32_t phase, int32_t resi
       out = describe_stream(a, o);
     } else if (step == 1) {
       const int64_t n0 = D.level_begin.size() > 1 ? D.level_begin[1] - D.level_begin[0] : 0;
-      TailArgs t{D.ctasks, n0, 0, nullptr, D.n_slots, D.empty, D.n_empty_pieces, b, A, D.rows,
-                 res ? A : nullptr, 1.0f, 0, 0};
+      const bool prefill = prefill_rows(kb, D, b, res);
+      TailArgs t{D.ctasks, n0, 0, nullptr, D.n_slots, D.empty, prefill ? 0 : D.n_empty_pieces, b, A,
+                 D.rows, res ? A : nullptr, 1.0f, 0, 0};
       out = describe_tail(t);
+      if (prefill) out = describe_fill(res) + (out.empty() ? "" : " + " + out);
     } else if (D.level_begin.size() > 2) {
       out = describe_combine(b);
     }
@@ -854,7 +859,7 @@ kb_status kb_profile_read(kb_t *kb, double *ms, int64_t *launches) {
     if (e == hipSuccess) e = hipEventElapsedTime(&el, r.start, r.stop);
     if (e != hipSuccess && st == KB_OK) st = hip_fail(e, "hipEventElapsedTime");
     if (ms) ms[r.phase] += el;
-    if (launches) ++launches[r.phase];
+    if (launches && r.counts) ++launches[r.phase];
     t.pool.push_back(r.start);
     t.pool.push_back(r.stop);
   }

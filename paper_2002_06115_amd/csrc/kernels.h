@@ -136,6 +136,7 @@ hipError_t launch_tail(const TailArgs &a, hipStream_t s);
 // +0.0, or gamma * res[i] when res is not null, to n floats (at most 2^33)
 // from p on, in one contiguous sweep; res must not overlap p.
 hipError_t launch_fill(float *p, int64_t n, const float *res, float gamma, hipStream_t s);
+std::string describe_fill(bool res);
 std::string describe_tail(const TailArgs &a);
 std::string describe_combine(int32_t b);
 

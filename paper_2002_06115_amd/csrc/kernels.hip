@@ -1418,6 +1418,8 @@ std::string describe_stream(const StreamArgs &a, const StreamOptions &o) {
   return buf;
 }
 
+std::string describe_fill(bool res) { return std::string("fill_kernel<") + tf(res) + ">"; }
+
 std::string describe_tail(const TailArgs &a) {
   if (a.n_tasks == 0 && a.n_pieces == 0) return "";
   const ColumnTiling t = column_tiling(a.b);
