@@ -136,12 +136,6 @@ typedef enum {
  *                                       variant, every pass (default: 32, 8
  *                                       for dR from b = 128; bitwise the
  *                                       same);
- *   KBFOLLOW_NARROW=0                   b <= 4 in the stream kernel (a lane
- *                                       group per chunk) instead of the narrow
- *                                       one (a lane per entry); another
- *                                       summation order
- *   KBFOLLOW_SCALAR_LANES=1             one float per lane wherever b is not
- *                                       a multiple of 4 (default: below b = 5)
  *   KBFOLLOW_PREFILL=0|1                rows without triples written one by
  *                                       one / by a sweep over the whole output
  *                                       before the stream kernel (default: by

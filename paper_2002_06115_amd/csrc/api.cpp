@@ -84,8 +84,6 @@ struct kb_t {
   bool plain_loads = false;  // force plain loads instead of raw buffer loads (testing)
   bool b_in_lds = true;      // stage small B tables in LDS (off: B rows in registers)
   int prefill = -1;          // empty rows by a sweep over the whole output: -1 by prefill_rows, 0 never, 1 always
-  bool narrow = true;        // the narrow kernel for b <= kMaxNarrow (off: the stream kernel; testing)
-  bool scalar_lanes = false; // one float per lane wherever b % 4 != 0 (testing)
   bool stream_stamps = true; // time stream kernels by their dispatch timestamps (off: event records)
   int max_lpt = 0;           // widest lane group of the register variant; 0: per pass (lane_cap)
   // The backward's dR pass on a stream of the KB's own, concurrent with the
@@ -303,8 +301,6 @@ kb_status run_pass(const kb_t *kb, const DevLayout &D, int ph_base, const float 
     StreamOptions o;
     o.plain_loads = kb->plain_loads;
     o.b_in_lds = kb->b_in_lds;
-    o.narrow = kb->narrow;
-    o.scalar_lanes = kb->scalar_lanes;
     o.n_cu = kb->n_cu;
     o.max_lpt = lane_cap(kb, ph_base, b);
     hipError_t e = launch_stream(a, o, s, scope.launch_start(), scope.launch_stop());
@@ -434,8 +430,6 @@ kb_status kb_create(int64_t n_entities, int64_t n_relations, int64_t n_triples,
     if (kb->n_cu <= 0) kb->n_cu = 1;
     kb->plain_loads = env_int("KBFOLLOW_PLAIN_LOADS", 0) != 0;
     kb->b_in_lds = env_int("KBFOLLOW_B_IN_LDS", 1) != 0;
-    kb->narrow = env_int("KBFOLLOW_NARROW", 1) != 0;
-    kb->scalar_lanes = env_int("KBFOLLOW_SCALAR_LANES", 0) != 0;
     kb->prefill = env_int("KBFOLLOW_PREFILL", -1);
     kb->stream_stamps = env_int("KBFOLLOW_STREAM_STAMPS", 1) != 0;
     kb->max_lpt = env_int("KBFOLLOW_MAX_LPT", 0);
@@ -815,8 +809,6 @@ kb_status kb_phase_kernel(const kb_t *kb, int32_t b, int32_t phase, int32_t resi
       StreamOptions o;
       o.plain_loads = kb->plain_loads;
       o.b_in_lds = kb->b_in_lds;
-      o.narrow = kb->narrow;
-      o.scalar_lanes = kb->scalar_lanes;
       o.n_cu = kb->n_cu;
       o.max_lpt = lane_cap(kb, pass * 3, b);
       out = describe_stream(a, o);

@@ -24,9 +24,8 @@ constexpr int kNarrowLanes = 8;
 // Narrowest row that is read 4 floats per lane where b % 4 != 0.
 constexpr int kMinRagged = 5;
 ColumnTiling column_tiling(int32_t b);
-// The same with lane groups of at most max_lpt lanes (a power of two <= 32);
-// scalar: one float per lane wherever b % 4 != 0.
-ColumnTiling column_tiling_max(int32_t b, int max_lpt, bool scalar = false);
+// The same with lane groups of at most max_lpt lanes (a power of two <= 32).
+ColumnTiling column_tiling_max(int32_t b, int max_lpt);
 
 // Chunk lengths must be multiples of this (the kernel's step, kUnroll entries).
 constexpr int32_t kChunkQuantum = 8;
@@ -87,11 +86,6 @@ struct StreamOptions {
   // rows in registers, the variant used for larger tables.
   bool b_in_lds = true;
   int n_cu = 1;  // compute units of the device, for the LDS variant's grid
-  // b <= kMaxNarrow takes the narrow kernel; off: the stream kernel's layouts.
-  bool narrow = true;
-  // One float per lane wherever b % 4 != 0 (the layout of b < 5), so that the
-  // two layouts can be compared.
-  bool scalar_lanes = false;
   int max_lpt = 32;  // widest lane group of the register variant (narrower: more column slices)
 };
 // With start / stop events the kernel is launched with hipExtLaunchKernel,

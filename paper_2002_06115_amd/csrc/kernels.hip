@@ -55,8 +55,6 @@ typedef float kbf_float4 __attribute__((ext_vector_type(4)));
 __device__ kbf_float4 struct_buffer_load_f32x4(__amdgpu_buffer_rsrc_t rsrc, int idx, int off,
                                                int soff, int aux)
     __asm("llvm.amdgcn.struct.ptr.buffer.load.v4f32");
-__device__ float struct_buffer_load_f32(__amdgpu_buffer_rsrc_t rsrc, int idx, int off, int soff,
-                                        int aux) __asm("llvm.amdgcn.struct.ptr.buffer.load.f32");
 
 namespace kbf {
 
@@ -150,51 +148,36 @@ __device__ __forceinline__ void load_row(const float *__restrict__ p, float (&v)
 // Record index that no table of this library reaches.
 constexpr uint32_t kNoRecord = 0xFFFFFFFFu;
 
-// VEC floats at byte `off` of record `idx` of a structured buffer (zeros when
+// 4 floats at byte `off` of record `idx` of a structured buffer (zeros when
 // idx is past its last record).
-template <int VEC>
 __device__ __forceinline__ void gather_row(__amdgpu_buffer_rsrc_t rsrc, uint32_t idx,
-                                           uint32_t off, float (&v)[VEC]) {
-  if constexpr (VEC == 4) {
-    const native_float4 t = struct_buffer_load_f32x4(rsrc, (int)idx, (int)off, 0, 0);
-    v[0] = t[0];
-    v[1] = t[1];
-    v[2] = t[2];
-    v[3] = t[3];
-  } else {
-    v[0] = struct_buffer_load_f32(rsrc, (int)idx, (int)off, 0, 0);
-  }
+                                           uint32_t off, float (&v)[4]) {
+  const native_float4 t = struct_buffer_load_f32x4(rsrc, (int)idx, (int)off, 0, 0);
+  v[0] = t[0];
+  v[1] = t[1];
+  v[2] = t[2];
+  v[3] = t[3];
 }
 
-// VEC floats at byte offset `off` of a raw buffer (zeros when off is past its end).
-template <int VEC>
+// 4 floats at byte offset `off` of a raw buffer (zeros when off is past its end).
 __device__ __forceinline__ void load_row_buffer(__amdgpu_buffer_rsrc_t rsrc, uint32_t off,
-                                                float (&v)[VEC]) {
-  if constexpr (VEC == 4) {
-    const auto t = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)off, 0, 0);
-    v[0] = __int_as_float(t[0]);
-    v[1] = __int_as_float(t[1]);
-    v[2] = __int_as_float(t[2]);
-    v[3] = __int_as_float(t[3]);
-  } else {
-    v[0] = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)off, 0, 0));
-  }
+                                                float (&v)[4]) {
+  const auto t = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)off, 0, 0);
+  v[0] = __int_as_float(t[0]);
+  v[1] = __int_as_float(t[1]);
+  v[2] = __int_as_float(t[2]);
+  v[3] = __int_as_float(t[3]);
 }
 
-// VEC floats of LDS at p (16-byte aligned when VEC = 4).
-template <int VEC>
-__device__ __forceinline__ void lds_row(const float *p, float (&v)[VEC]) {
-  if constexpr (VEC == 4) {
-    const native_float4 t = *reinterpret_cast<const native_float4 *>(p);
-    v[0] = t[0];
-    v[1] = t[1];
-    v[2] = t[2];
-    v[3] = t[3];
-  } else {
-    v[0] = *p;
-  }
+// 4 floats of LDS at p (16-byte aligned).
+__device__ __forceinline__ void lds_row(const float *p, float (&v)[4]) {
+  const native_float4 t = *reinterpret_cast<const native_float4 *>(p);
+  v[0] = t[0];
+  v[1] = t[1];
+  v[2] = t[2];
+  v[3] = t[3];
 }
-// The columns a lane of VEC floats works on, c0 being where its place in the
+// The columns a lane of 4 floats works on, c0 being where its place in the
 // row begins (c0 < b).  Rows of b floats, b not a multiple of 4, end in a lane
 // whose 4 columns would pass the row's end: it takes the last 4 of the row
 // instead (so that every 16-byte load stays inside its row; b >= 5 there).
@@ -218,12 +201,8 @@ __device__ __forceinline__ LaneCols lane_cols(int c0, int b) {
   }
 }
 
-template <int VEC>
-__device__ __forceinline__ void lds_store(float *p, const float (&v)[VEC]) {
-  if constexpr (VEC == 4)
-    *reinterpret_cast<native_float4 *>(p) = native_float4{v[0], v[1], v[2], v[3]};
-  else
-    *p = v[0];
+__device__ __forceinline__ void lds_store(float *p, const float (&v)[4]) {
+  *reinterpret_cast<native_float4 *>(p) = native_float4{v[0], v[1], v[2], v[3]};
 }
 
 // Output rows are written once and not read again by the pass: non-temporal
@@ -287,36 +266,24 @@ __device__ __forceinline__ void store_slot_from(double *__restrict__ p, const do
   }
 }
 
-template <int VEC>
 __device__ __forceinline__ void store_slot_buffer(__amdgpu_buffer_rsrc_t rsrc, uint32_t off,
-                                                  const double (&acc)[VEC]) {
+                                                  const double (&acc)[4]) {
   typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-  typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-  if constexpr (VEC == 4) {
-    const double2 lo = make_double2(acc[0], acc[1]), hi = make_double2(acc[2], acc[3]);
-    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, lo), rsrc, (int)off, 0, 0);
-    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, hi), rsrc, (int)(off + 16), 0,
-                                           0);
-  } else {
-    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, acc[0]), rsrc, (int)off, 0, 0);
-  }
+  const double2 lo = make_double2(acc[0], acc[1]), hi = make_double2(acc[2], acc[3]);
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, lo), rsrc, (int)off, 0, 0);
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, hi), rsrc, (int)(off + 16), 0,
+                                         0);
 }
 
-// Stores of VEC floats / doubles at byte offset `off` of a raw buffer; rows
+// Stores of 4 floats / doubles at byte offset `off` of a raw buffer; rows
 // written once per pass use the non-temporal policy.
 constexpr int kNonTemporal = 2;
-template <int VEC>
 __device__ __forceinline__ void store_row_buffer(__amdgpu_buffer_rsrc_t rsrc, uint32_t off,
-                                                 const double (&y)[VEC]) {
-  if constexpr (VEC == 4) {
-    const native_float4 v = {(float)y[0], (float)y[1], (float)y[2], (float)y[3]};
-    __builtin_amdgcn_raw_buffer_store_b128(
-        __builtin_bit_cast(__attribute__((ext_vector_type(4))) unsigned int, v), rsrc, (int)off, 0,
-        kNonTemporal);
-  } else {
-    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint((float)y[0]), rsrc, (int)off, 0,
-                                          kNonTemporal);
-  }
+                                                 const double (&y)[4]) {
+  const native_float4 v = {(float)y[0], (float)y[1], (float)y[2], (float)y[3]};
+  __builtin_amdgcn_raw_buffer_store_b128(
+      __builtin_bit_cast(__attribute__((ext_vector_type(4))) unsigned int, v), rsrc, (int)off, 0,
+      kNonTemporal);
 }
 
 // One lane group (LPT lanes) per chunk of the entry stream; chunks are
@@ -359,20 +326,21 @@ __device__ __forceinline__ void store_row_buffer(__amdgpu_buffer_rsrc_t rsrc, ui
 // inside the loop and ran slower, so they keep the compiler's own
 // allocation.
 constexpr int kRaggedLane = -4;
-template <int LANE, int LPT, bool WEIGHTED, bool RES, bool LDSB>
+template <int LPT, bool WEIGHTED, bool RES, bool LDSB>
 constexpr int stream_min_waves() {
-  return (LDSB && !WEIGHTED && LANE != 1 && (RES ? LPT >= 8 : LPT == 8)) ? 6 : 1;
+  return (LDSB && !WEIGHTED && (RES ? LPT >= 8 : LPT == 8)) ? 6 : 1;
 }
 
 //
-// LANE: floats per lane, 1 or 4, or kRaggedLane: 4 where b >= 5 is not a
-// multiple of 4 (see LaneCols).
+// LANE: 4 floats per lane, or kRaggedLane: 4 where b >= 5 is not a multiple of 4
+// (see LaneCols).
 template <int LANE, int LPT, bool BUF, bool WEIGHTED, bool RES, bool LDSB>
 __global__ __launch_bounds__((LDSB ? kBlockLdsBig : kBlock),
-                             (stream_min_waves<LANE, LPT, WEIGHTED, RES, LDSB>())) void
+                             (stream_min_waves<LPT, WEIGHTED, RES, LDSB>())) void
 stream_kernel(StreamArgs a) {
   constexpr bool RAGGED = LANE == kRaggedLane;
-  constexpr int VEC = RAGGED ? 4 : LANE;
+  static_assert(LANE == 4 || RAGGED, "narrower rows have a kernel of their own");
+  constexpr int VEC = 4;
   static_assert(BUF || !LDSB, "the LDS copy of B goes with raw buffer loads");
   const int BLK = LDSB ? (int)blockDim.x : kBlock;  // kBlockLds or kBlockLdsBig
   const int GPB = BLK / LPT;
@@ -460,7 +428,7 @@ stream_kernel(StreamArgs a) {
 #pragma unroll
         for (int q = 0; q < VEC; ++q) v[q] = 0.0f;
       }
-      lds_store<VEC>(b_lds + i, v);
+      lds_store(b_lds + i, v);
     }
     __syncthreads();
   }
@@ -560,12 +528,12 @@ stream_kernel(StreamArgs a) {
 #else
           const uint32_t ra = same_a ? kNoRecord : ((uint32_t)e[u].x & ~(uint32_t)kRunStart);
 #endif
-          gather_row<VEC>(arsrc, ra, col_bytes, xa[u]);
+          gather_row(arsrc, ra, col_bytes, xa[u]);
           if constexpr (!LDSB)
-            gather_row<VEC>(brsrc, run_start ? (uint32_t)KBF_CHECKED(bid, a.B_rows) : kNoRecord,
+            gather_row(brsrc, run_start ? (uint32_t)KBF_CHECKED(bid, a.B_rows) : kNoRecord,
                             col_bytes, xb[u]);
         } else if constexpr (BUF) {
-          load_row_buffer<VEC>(
+          load_row_buffer(
               arsrc,
               (triple || res_row)
                   ? (uint32_t)KBF_CHECKED(ia, triple ? a.A_rows : a.out_rows) * row_bytes +
@@ -573,7 +541,7 @@ stream_kernel(StreamArgs a) {
                   : kOutOfRange,
               xa[u]);
           if constexpr (!LDSB)
-            load_row_buffer<VEC>(brsrc,
+            load_row_buffer(brsrc,
                                  run_start ? (uint32_t)KBF_CHECKED(bid, a.B_rows) * row_bytes +
                                                  col_bytes
                                            : kOutOfRange,
@@ -611,7 +579,7 @@ stream_kernel(StreamArgs a) {
         // out-of-range B load returned (masked explicitly without BUF).
         if constexpr (LDSB) {
           if (run_start) {
-            lds_row<VEC>(b_lds + (size_t)KBF_CHECKED(e[u].y & kIdMask, a.B_rows) * W + lane * VEC,
+            lds_row(b_lds + (size_t)KBF_CHECKED(e[u].y & kIdMask, a.B_rows) * W + lane * VEC,
                          held_b);
           } else if (!triple) {
 #pragma unroll
@@ -645,13 +613,13 @@ stream_kernel(StreamArgs a) {
                                    skip);
           } else if (f >= 0) {
             if constexpr (BUF)
-              store_row_buffer<VEC>(
+              store_row_buffer(
                   orsrc, (uint32_t)KBF_CHECKED(f, a.out_rows) * row_bytes + col_bytes, y);
             else
               store_row<VEC>(a.out + (size_t)KBF_CHECKED(f, a.out_rows) * bb + c, y);
           } else {
             if constexpr (BUF)
-              store_slot_buffer<VEC>(
+              store_slot_buffer(
                   srsrc,
                   ((uint32_t)KBF_CHECKED(-(f + 1), a.n_slots) * (uint32_t)a.b + (uint32_t)c) *
                       (uint32_t)sizeof(double),
@@ -1110,9 +1078,8 @@ template <int LANE, bool BUF, bool WT, bool RES, bool LDSB>
 const void *stream_fn(int lpt) {
   switch (lpt) {
     case 1:
-      // (One lane per group of a row of 5 floats or more: KBFOLLOW_MAX_LPT=1,
-      // which does not narrow the LDS variant's groups.)
-      if constexpr (LANE == kRaggedLane && LDSB)
+      // (KBFOLLOW_MAX_LPT=1, which does not narrow the LDS variant's groups.)
+      if constexpr (LDSB)
         return nullptr;
       else
         return reinterpret_cast<const void *>(&stream_kernel<LANE, 1, BUF, WT, RES, LDSB>);
@@ -1141,14 +1108,9 @@ const void *stream_fn_for(const ColumnTiling &t, bool buf, bool lds, bool wt, bo
     return lds ? stream_fn_sel<kRaggedLane, true, true>(t.lpt, wt, res)
                : stream_fn_sel<kRaggedLane, true, false>(t.lpt, wt, res);
   }
-  if (t.vec == 4) {
-    if (!buf) return stream_fn_sel<4, false, false>(t.lpt, wt, res);
-    return lds ? stream_fn_sel<4, true, true>(t.lpt, wt, res)
-               : stream_fn_sel<4, true, false>(t.lpt, wt, res);
-  }
-  if (!buf) return stream_fn_sel<1, false, false>(t.lpt, wt, res);
-  return lds ? stream_fn_sel<1, true, true>(t.lpt, wt, res)
-             : stream_fn_sel<1, true, false>(t.lpt, wt, res);
+  if (!buf) return stream_fn_sel<4, false, false>(t.lpt, wt, res);
+  return lds ? stream_fn_sel<4, true, true>(t.lpt, wt, res)
+             : stream_fn_sel<4, true, false>(t.lpt, wt, res);
 }
 
 template <int N, bool LDSB>
@@ -1228,7 +1190,7 @@ int64_t blocks_for(int64_t items, int per_block, int max_blocks) {
 
 ColumnTiling column_tiling(int32_t b) { return column_tiling_max(b, kMaxLpt); }
 
-ColumnTiling column_tiling_max(int32_t b, int max_lpt, bool scalar) {
+ColumnTiling column_tiling_max(int32_t b, int max_lpt) {
   ColumnTiling t;
   // Rows whose width is not a multiple of 4 are read 4 floats per lane too,
   // from 5 floats on (see LaneCols): one float per lane needs up to four
@@ -1236,7 +1198,7 @@ ColumnTiling column_tiling_max(int32_t b, int max_lpt, bool scalar) {
   // follows (forward stream kernel at b = 10 on a KB of 12.9 M entities and
   // 43.7 M triples 2680 -> 780 us, at b = 93 on one of 43 k entities and 190 k
   // triples 47 -> 19 us).
-  t.ragged = b % 4 != 0 && b >= kMinRagged && !scalar;
+  t.ragged = b % 4 != 0 && b >= kMinRagged;
   t.vec = (b % 4 == 0 || t.ragged) ? 4 : 1;
   const int lanes = (b + t.vec - 1) / t.vec;
   // Lane groups of at most kMaxLpt lanes: wider rows are cut into column
@@ -1266,7 +1228,7 @@ struct StreamChoice {
 };
 
 hipError_t choose_stream(const StreamArgs &a, const StreamOptions &o, StreamChoice *c) {
-  const ColumnTiling t = column_tiling_max(a.b, kMaxLpt, o.scalar_lanes);
+  const ColumnTiling t = column_tiling_max(a.b, kMaxLpt);
   if (a.chunk % kChunkQuantum != 0 || a.n % a.chunk != 0) return hipErrorInvalidValue;
   // Raw-buffer offsets are 32-bit and a structured buffer's record stride is
   // at most kMaxStride bytes: tables of 4 GB or more, or rows of more than
@@ -1297,7 +1259,7 @@ hipError_t choose_stream(const StreamArgs &a, const StreamOptions &o, StreamChoi
     longest = std::max<int64_t>(longest, a.list_chunk[x + 1] - a.list_chunk[x]);
   }
   const int nl = a.n_lists;
-  if (a.b <= kMaxNarrow && o.narrow) {
+  if (a.b <= kMaxNarrow) {
     const size_t table = (size_t)a.B_rows * (size_t)a.b * sizeof(float);
     const bool lds = o.b_in_lds && table <= kNarrowLds;
     constexpr int64_t groups = kBlock / kNarrowLanes;
@@ -1320,7 +1282,7 @@ hipError_t choose_stream(const StreamArgs &a, const StreamOptions &o, StreamChoi
   }
   // The register variant's lane groups: at most o.max_lpt lanes wide.
   const ColumnTiling tr =
-      column_tiling_max(a.b, std::max(1, std::min(o.max_lpt, kMaxLpt)), o.scalar_lanes);
+      column_tiling_max(a.b, std::max(1, std::min(o.max_lpt, kMaxLpt)));
   const void *reg_fn = stream_fn_for(tr, buf, false, wt, res);
   if (!reg_fn) return hipErrorInvalidValue;
   c->buf = buf;
@@ -1330,9 +1292,8 @@ hipError_t choose_stream(const StreamArgs &a, const StreamOptions &o, StreamChoi
   c->ragged = t.ragged;
   // B's column slice in LDS when it fits and the LDS variant keeps at least
   // as many waves on a CU as the register variant: where it needs more
-  // registers per lane than its workgroup can be given (b = 4 .. 16, the
-  // soft KB), or where the register variant runs at eight waves per SIMD
-  // already (b = 1), B stays in registers.  A slice of at most kMaxLdsB bytes
+  // registers per lane than its workgroup can be given (b = 5 .. 16, the
+  // soft KB), B stays in registers.  A slice of at most kMaxLdsB bytes
   // goes with two 768-thread workgroups per CU; for the hard KB a slice of up
   // to kMaxLdsBig bytes goes with one 1024-thread workgroup, and rows wider
   // than 32 columns whose slice is too large are cut into 32-column slices
@@ -1343,8 +1304,8 @@ hipError_t choose_stream(const StreamArgs &a, const StreamOptions &o, StreamChoi
     const bool hard = !wt && !res;
     ColumnTiling tl = t;
     size_t lds_bytes = (size_t)a.B_rows * (size_t)tl.width * sizeof(float);
-    if (hard && lds_bytes > kMaxLdsB && t.vec == 4 && t.width > 32) {
-      tl = column_tiling_max(a.b, 8, o.scalar_lanes);
+    if (hard && lds_bytes > kMaxLdsB && t.width > 32) {
+      tl = column_tiling_max(a.b, 8);
       lds_bytes = (size_t)a.B_rows * (size_t)tl.width * sizeof(float);
     }
     const int blk = lds_bytes <= kMaxLdsB ? kBlockLds : kBlockLdsBig;

@@ -1,7 +1,8 @@
 """Widths that are not a multiple of 4: rows read 4 floats per lane, their last
 lane taking the row's last 4 columns, against the oracle and, bit for bit,
-against one float per lane (the sums and their order are the same), with the
-rows no triple reaches written one by one or by a sweep over the output."""
+against the same columns of a call padded to the next multiple of 4 (a column's
+sums and their order are the same), with the rows no triple reaches written one
+by one or by a sweep over the output."""
 import numpy as np
 import pytest
 
@@ -64,11 +65,11 @@ def test_ragged_widths(kbf, b, weighted, path, monkeypatch):
     assert_close(got[3], dXo, "dX")
     assert_close(got[4], dRo, "dR")
     monkeypatch.setenv("KBFOLLOW_PREFILL", "0")
-    monkeypatch.setenv("KBFOLLOW_SCALAR_LANES", "1")
-    want = outputs(kbf, kb_args, n_e, n_r, *dev, w)
+    pad = lambda a: np.concatenate([a, np.ones((-b % 4, a.shape[1]), np.float32)])  # noqa: E731
+    want = outputs(kbf, kb_args, n_e, n_r, *(to_em(pad(a)) for a in (X, R, dY, Z)), w)
     for name, a, c in zip(("Y", "Y residual", "Z", "dX", "dR", "dX residual", "dR residual"),
                           got, want):
-        assert np.array_equal(a, c), (name, b, weighted, path)
+        assert np.array_equal(a, c[:b]), (name, b, weighted, path)
 
 
 # Every cap on the lanes of a group, one lane included, at the narrowest row, a
