@@ -104,10 +104,12 @@ typedef enum {
  *                                       chunk's end or not;
  *   KBFOLLOW_PLAIN_LOADS=1              plain loads instead of raw buffer
  *                                       loads (bitwise the same);
- *   KBFOLLOW_B_IN_LDS=0                 the second operand (R, or X for dR)
+ *   KBFOLLOW_B_IN_LDS=0|2               the second operand (R, or X for dR)
  *                                       read into registers per run even
- *                                       where its table fits LDS (bitwise
- *                                       the same);
+ *                                       where its table fits LDS / staged in
+ *                                       LDS wherever it fits (default 1: where
+ *                                       the KB spreads over the chip and
+ *                                       enough waves fit; bitwise the same);
  *   KBFOLLOW_LAYOUT_SORT=counting       the chained counting sorts for
  *                                       every KB (bitwise the same);
  *   KBFOLLOW_OVERLAP_BACKWARD=0|1       dR concurrent with dX on the KB's

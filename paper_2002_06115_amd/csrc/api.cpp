@@ -82,7 +82,7 @@ struct kb_t {
   int64_t n_entities = 0, n_relations = 0, n_triples = 0;
   bool weighted = false;
   bool plain_loads = false;  // force plain loads instead of raw buffer loads (testing)
-  bool b_in_lds = true;      // stage small B tables in LDS (off: B rows in registers)
+  int b_in_lds = 1;          // stage small B tables in LDS (see StreamOptions)
   int prefill = -1;          // empty rows by a sweep over the whole output: -1 by prefill_rows, 0 never, 1 always
   bool stream_stamps = true; // time stream kernels by their dispatch timestamps (off: event records)
   int max_lpt = 0;           // widest lane group of the register variant; 0: per pass (lane_cap)
@@ -429,7 +429,7 @@ kb_status kb_create(int64_t n_entities, int64_t n_relations, int64_t n_triples,
       kb->n_cu = v;
     if (kb->n_cu <= 0) kb->n_cu = 1;
     kb->plain_loads = env_int("KBFOLLOW_PLAIN_LOADS", 0) != 0;
-    kb->b_in_lds = env_int("KBFOLLOW_B_IN_LDS", 1) != 0;
+    kb->b_in_lds = env_int("KBFOLLOW_B_IN_LDS", 1);
     kb->prefill = env_int("KBFOLLOW_PREFILL", -1);
     kb->stream_stamps = env_int("KBFOLLOW_STREAM_STAMPS", 1) != 0;
     kb->max_lpt = env_int("KBFOLLOW_MAX_LPT", 0);

@@ -82,9 +82,10 @@ struct StreamOptions {
   // Forces the plain-load variant (used anyway for tables of 4 GB or more)
   // so it can be tested at small sizes.
   bool plain_loads = false;
-  // Stage B in LDS when its slice fits (raw-buffer path only); off keeps B
-  // rows in registers, the variant used for larger tables.
-  bool b_in_lds = true;
+  // Stage B in LDS when its slice fits (raw-buffer path only): 0 keeps B rows in
+  // registers, the variant used for larger tables; 1 where choose_stream's rules
+  // on spread and occupancy take it; 2 wherever it fits (testing).
+  int b_in_lds = 1;
   int n_cu = 1;  // compute units of the device, for the LDS variant's grid
   int max_lpt = 32;  // widest lane group of the register variant (narrower: more column slices)
 };

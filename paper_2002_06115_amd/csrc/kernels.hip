@@ -1261,7 +1261,7 @@ hipError_t choose_stream(const StreamArgs &a, const StreamOptions &o, StreamChoi
   const int nl = a.n_lists;
   if (a.b <= kMaxNarrow) {
     const size_t table = (size_t)a.B_rows * (size_t)a.b * sizeof(float);
-    const bool lds = o.b_in_lds && table <= kNarrowLds;
+    const bool lds = o.b_in_lds != 0 && table <= kNarrowLds;
     constexpr int64_t groups = kBlock / kNarrowLanes;
     int64_t per_list = std::max<int64_t>(1, (longest + groups - 1) / groups);
     // With B in LDS each workgroup copies it, so there are only so many (eight
@@ -1300,7 +1300,7 @@ hipError_t choose_stream(const StreamArgs &a, const StreamOptions &o, StreamChoi
   // (one 128-byte line of every row each) when that makes B fit.  The grid
   // is as many workgroups as the CUs hold at once, each copying its slice of
   // the table once and walking its chunks grid-stride.
-  if (buf && o.b_in_lds) {
+  if (buf && o.b_in_lds != 0) {
     const bool hard = !wt && !res;
     ColumnTiling tl = t;
     size_t lds_bytes = (size_t)a.B_rows * (size_t)tl.width * sizeof(float);
@@ -1321,7 +1321,8 @@ hipError_t choose_stream(const StreamArgs &a, const StreamOptions &o, StreamChoi
       // against 5.6 / 5.6).
       const bool spreads =
           longest * nl * tl.n_slices >= (int64_t)(o.n_cu > 0 ? o.n_cu : 1) * (blk / tl.lpt);
-      if (spreads && per_cu > 0 && per_cu * blk >= reg_per_cu * kBlock) {
+      if (per_cu > 0 &&
+          (o.b_in_lds > 1 || (spreads && per_cu * blk >= reg_per_cu * kBlock))) {
         const int64_t cap = (int64_t)per_cu * (o.n_cu > 0 ? o.n_cu : 1);
         const int64_t per_list = std::max<int64_t>(1, std::min<int64_t>(
             (longest + blk / tl.lpt - 1) / (blk / tl.lpt), cap / nl));

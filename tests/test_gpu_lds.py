@@ -2,7 +2,8 @@
 slice of B staged in LDS (up to 80 KB with two workgroups per CU, up to 160 KB
 with one for the hard KB, rows cut into 32-column slices where that makes B
 fit; used when the LDS variant keeps at least as many waves on a CU as the
-register variant), or one B row per run loaded into registers.  Both do the
+register variant and the KB spreads over the chip, which these small ones do
+not: it is forced here), or one B row per run loaded into registers.  Both do the
 same FMAs in the same order, so their outputs must agree bit for bit, and
 both must match the oracle.  The KBs sit on either side of the 80 KB and
 160 KB limits (R with 640 / 641 and 1280 / 1281 rows at b = 32), need the
@@ -37,9 +38,14 @@ def kb_arrays(seed, n_e, n_r, n_t):
     return s.astype(np.int32), r.astype(np.int32), o.astype(np.int32)
 
 
-def run(kbf, monkeypatch, lds, s, r, o, n_e, n_r, X, R, dY, weight=None, gamma=None):
-    monkeypatch.setenv("KBFOLLOW_B_IN_LDS", "1" if lds else "0")
+def run(kbf, monkeypatch, lds, s, r, o, n_e, n_r, X, R, dY, weight=None, gamma=None, fits=True):
+    """Forward and backward with B in LDS wherever it fits, or never; the kernels'
+    names say that the forward and dX passes ran that way."""
+    monkeypatch.setenv("KBFOLLOW_B_IN_LDS", "2" if lds else "0")
     kb = kbf.KB(s, r, o, n_e, n_r, weight=weight)
+    names = kb.phase_kernels(X.shape[0], residual=gamma is not None)
+    for p in ("fwd_stream", "dx_stream"):
+        assert names[p].endswith("true>" if lds and fits else "false>"), (p, names[p])
     Y = from_em(kb.follow(to_em(X), to_em(R), residual=gamma))
     dX, dR = kb.follow_backward(to_em(X), to_em(R), to_em(dY), residual=gamma)
     out = Y, from_em(dX), from_em(dR)
@@ -58,7 +64,7 @@ def test_lds_and_register_paths_agree(kbf, monkeypatch, b, n_r):
     X = g.standard_normal((b, n_e)).astype(np.float32)
     R = g.standard_normal((b, n_r)).astype(np.float32)
     dY = g.standard_normal((b, n_e)).astype(np.float32)
-    with_lds = run(kbf, monkeypatch, True, s, r, o, n_e, n_r, X, R, dY)
+    with_lds = run(kbf, monkeypatch, True, s, r, o, n_e, n_r, X, R, dY, fits=(b, n_r) != (32, 1281))
     in_regs = run(kbf, monkeypatch, False, s, r, o, n_e, n_r, X, R, dY)
     for name, a, c in zip(("Y", "dX", "dR"), with_lds, in_regs):
         assert_bitexact(a, c, f"b={b} n_r={n_r} {name}: LDS vs registers")
@@ -88,7 +94,7 @@ def test_soft_and_residual_variants_agree(kbf, monkeypatch, b, weighted, gamma):
 def test_integer_inputs_exact_on_the_lds_path(kbf, monkeypatch):
     """k-hot X and one-hot R: every sum is an integer, so the result is the
     oracle's bit for bit (R with 600 rows at b = 32 sits in LDS)."""
-    monkeypatch.setenv("KBFOLLOW_B_IN_LDS", "1")
+    monkeypatch.setenv("KBFOLLOW_B_IN_LDS", "2")
     n_e, n_r, n_t, b = 20_000, 600, 200_000, 32
     s, r, o = kb_arrays(99, n_e, n_r, n_t)
     g = np.random.default_rng(99)
@@ -100,6 +106,7 @@ def test_integer_inputs_exact_on_the_lds_path(kbf, monkeypatch):
     R[np.arange(b), g.integers(0, 8, b)] = 1.0
     dY = np.ones((b, n_e), np.float32)
     kb = kbf.KB(s, r, o, n_e, n_r)
+    assert kb.phase_kernels(b)["fwd_stream"].endswith("true>")
     Y = from_em(kb.follow(to_em(X), to_em(R)))
     dX, dR = kb.follow_backward(to_em(X), to_em(R), to_em(dY))
     assert_bitexact(Y, oracle.follow(s, r, o, n_e, n_r, X, R), "Y")

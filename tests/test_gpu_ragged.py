@@ -46,8 +46,7 @@ def test_ragged_widths(kbf, b, weighted, path, monkeypatch):
     if path == "plain":
         monkeypatch.setenv("KBFOLLOW_PLAIN_LOADS", "1")
     monkeypatch.setenv("KBFOLLOW_PREFILL", "1" if path == "prefill" else "0")
-    if path == "regs":
-        monkeypatch.setenv("KBFOLLOW_B_IN_LDS", "0")
+    monkeypatch.setenv("KBFOLLOW_B_IN_LDS", "2" if path in ("lds", "prefill") else "0")
     g = np.random.default_rng(b)
     n_e, n_r, n_t = 300, 7, 5000
     s = np.where(g.random(n_t) < 0.3, g.integers(0, 3, n_t), g.integers(0, n_e, n_t))
@@ -58,13 +57,20 @@ def test_ragged_widths(kbf, b, weighted, path, monkeypatch):
     draw = lambda n: g.standard_normal((b, n)).astype(np.float32)  # noqa: E731
     X, R, dY, Z = draw(n_e), draw(n_r), draw(n_e), draw(n_e)
     dev = [to_em(a) for a in (X, R, dY, Z)]
+    kb = kbf.KB(*kb_args, n_e, n_r, weight=w)
+    for residual in (False, True):
+        name = kb.phase_kernels(b, residual=residual)["fwd_stream"]
+        assert name.startswith("stream_kernel<-4, "), name
+        assert name.endswith("true>" if path in ("lds", "prefill") else "false>"), name
+    kb.close()
     got = outputs(kbf, kb_args, n_e, n_r, *dev, w)
     Yo = oracle.follow(*kb_args, n_e, n_r, X, R, weight=w)
     dXo, dRo = oracle.follow_backward(*kb_args, n_e, n_r, X, R, dY, weight=w)
     assert_close(got[0], Yo, "Y")
     assert_close(got[3], dXo, "dX")
     assert_close(got[4], dRo, "dR")
-    monkeypatch.setenv("KBFOLLOW_PREFILL", "0")
+    for name in ("PREFILL", "PLAIN_LOADS", "B_IN_LDS"):
+        monkeypatch.setenv("KBFOLLOW_" + name, "0")
     pad = lambda a: np.concatenate([a, np.ones((-b % 4, a.shape[1]), np.float32)])  # noqa: E731
     want = outputs(kbf, kb_args, n_e, n_r, *(to_em(pad(a)) for a in (X, R, dY, Z)), w)
     for name, a, c in zip(("Y", "Y residual", "Z", "dX", "dR", "dX residual", "dR residual"),

@@ -2,7 +2,7 @@
 
 Each case draws a KB shape (entities, relations, triples; uniform or
 Zipf-skewed ids), a batch width, a plan (chunk length, combine fan-in), a
-load path (B in LDS allowed or not, raw buffer or plain loads) and an
+load path (B in LDS where it fits or not, raw buffer or plain loads) and an
 operation (plain follow, soft KB, residual hop, accumulating follow), and
 compares forward and backward with the oracle: within rtol 1e-5 / atol 1e-7
 on real-valued inputs, bit for bit on integer-valued ones.  Relation counts
@@ -80,7 +80,7 @@ def test_random_shape(kbf, seed, monkeypatch):
     monkeypatch.setenv("KBFOLLOW_CHUNK", str(c["chunk"]))
     monkeypatch.setenv("KBFOLLOW_REL_CHUNK", str(c["chunk"]))
     monkeypatch.setenv("KBFOLLOW_FAN_IN", str(c["fan_in"]))
-    monkeypatch.setenv("KBFOLLOW_B_IN_LDS", "1" if c["lds"] else "0")
+    monkeypatch.setenv("KBFOLLOW_B_IN_LDS", "2" if c["lds"] else "0")
     monkeypatch.setenv("KBFOLLOW_PLAIN_LOADS", "1" if c["plain"] else "0")
     s, r, o, n_e, n_r = c["s"], c["r"], c["o"], c["n_e"], c["n_r"]
     X, R, dY, Z, gamma = c["X"], c["R"], c["dY"], c["Z"], c["gamma"]

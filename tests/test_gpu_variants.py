@@ -1,8 +1,9 @@
 """Every kernel variant against the oracle.
 
-The stream kernel is instantiated per lane layout (4 floats per lane when
-b % 4 == 0, else 1; lane groups of 1..32 lanes; column slices beyond 128
-columns), per load path (raw buffer loads with the B table staged in LDS or
+Rows of up to 4 floats have the narrow kernel, with B in LDS or not.  For wider
+ones the stream kernel is instantiated per lane layout (4 floats per lane, the
+last lane reaching back where b % 4 != 0; lane groups of up to 32 lanes; column
+slices beyond 128 columns), per load path (raw buffer loads with the B table staged in LDS or
 with B rows held in registers, or plain loads as for tables of 4 GB or more),
 per hard or soft KB (App. A weights) and per plain or residual
 hop (Sec. 3.2, App. E).  Each combination runs forward and backward on a KB
@@ -38,8 +39,9 @@ def small_kb(seed, n_e=300, n_r=7, n_t=6000):
     return s.astype(np.int32), r.astype(np.int32), o.astype(np.int32), n_e, n_r
 
 
-COMBOS = list(itertools.product([1, 4, 5, 36, 260], [False, True], [None, 0.5],
-                                ["lds", "regs", "plain"]))
+COMBOS = (list(itertools.product([1, 4], [False, True], [None, 0.5], ["lds", "regs"])) +
+          list(itertools.product([5, 36, 260, 261], [False, True], [None, 0.5],
+                                 ["lds", "regs", "plain"])))
 
 
 @pytest.mark.parametrize("b,weighted,gamma,path", COMBOS)
@@ -49,8 +51,7 @@ def test_variant(kbf, b, weighted, gamma, path, monkeypatch):
     monkeypatch.setenv("KBFOLLOW_FAN_IN", "3")
     if path == "plain":
         monkeypatch.setenv("KBFOLLOW_PLAIN_LOADS", "1")
-    if path == "regs":
-        monkeypatch.setenv("KBFOLLOW_B_IN_LDS", "0")
+    monkeypatch.setenv("KBFOLLOW_B_IN_LDS", "2" if path == "lds" else "0")
     s, r, o, n_e, n_r = small_kb(b * 7 + weighted)
     g = np.random.default_rng(b)
     w = g.uniform(0.1, 2.0, len(s)).astype(np.float32) if weighted else None
@@ -58,6 +59,12 @@ def test_variant(kbf, b, weighted, gamma, path, monkeypatch):
     R = g.standard_normal((b, n_r)).astype(np.float32)
     dY = g.standard_normal((b, n_e)).astype(np.float32)
     kb = kbf.KB(s, r, o, n_e, n_r, weight=w)
+    for p in ("fwd_stream", "dx_stream"):
+        name = kb.phase_kernels(b, residual=gamma is not None)[p]
+        flags = [f == "true" for f in name[name.index("<") + 1:-1].split(", ")[-3:]]
+        assert flags == [weighted, gamma is not None, path == "lds"], name
+        if b >= 5:
+            assert (name.split(", ")[2] == "true") == (path != "plain"), name
     Y = from_em(kb.follow(to_em(X), to_em(R), residual=gamma))
     dX, dR = kb.follow_backward(to_em(X), to_em(R), to_em(dY), residual=gamma)
     if gamma is None:
