@@ -465,8 +465,14 @@ int32_t default_chunk(int64_t entries) {
 int32_t entity_chunk(const LayoutHost &L, int64_t n_entities) {
   const int64_t entries = (int64_t)L.row.size() + n_entities;
   int32_t c = default_chunk(entries);
-  if (c <= 32 || entries / c >= 98304 || !local_ids(L)) return c;
-  while (c > 32 && entries / c < 98304 && hub_share(L.row, c / 16 + 1) <= 0.125) c /= 2;
+  // Few chunks yet, and few rows that half of c could split.
+  auto halve = [&]() {
+    return c > 32 && entries / c < 98304 && hub_share(L.row, c / 16 + 1) <= 0.125;
+  };
+  if (!halve()) return c;
+  if (c == 256) c = 128;
+  if (local_ids(L))
+    while (halve()) c /= 2;
   return c;
 }
 

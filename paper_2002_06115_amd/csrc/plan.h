@@ -159,17 +159,22 @@ bool local_ids(const LayoutHost &layout);
 int32_t default_chunk(int64_t entries);
 
 // Chunk length of the forward or dX layout over n_entities rows: the default, or
-// down to 32 entries for 96 K chunks where the gathered ids are local and at most
-// an eighth of the triples lie in rows longer than an eighth of the shorter chunk
-// (up to that length a row that does not fit in what is left of a chunk leaves it
-// to no-op markers, so packing splits none).  The rows in flight at once are then closer together, and
-// so is what they gather: grid of 10^6 cells, b = 128, 128 -> 32 entries: 336 ->
-// 300 us (b = 64: 170 -> 162, b = 10: 74 -> 62, b = 32: 77 -> 82).  With ids
-// spread evenly there is nothing to bring together, and the starts of more
-// chunks cost: 500 k entities with 10 triples each, b = 32, 128 -> 32 entries:
-// 114 -> 127 us; 300 k with 30 each, b = 32, 256 -> 64: 175 -> 191.  Rows longer
-// than a chunk add partials to that: 100 k entities with 80 triples each, b = 32,
-// 128 -> 64: 127 -> 148, and 67 k -> 220 k slots.
+// shorter, for 96 K chunks, where at most an eighth of the triples lie in rows
+// longer than an eighth of the shorter chunk (up to that length a row that does
+// not fit in what is left of a chunk leaves it to no-op markers, so packing splits
+// none).  Longer rows would add partials: 100 k entities with 80 triples each, b =
+// 32, 128 -> 64 entries: 127 -> 148 us, and 67 k -> 220 k slots.
+// - 128 entries instead of 256, forward at b = 1 / 10 / 32 / 64 / 128, us: 2 M
+//   entities, 20 M triples with Zipf subjects, 108 / 270 / 278 / 546 / 994 -> 106 /
+//   259 / 283 / 516 / 1002; 1.5 M, 14 M, 86 / 186 / 188 / 394 / 724 -> 81 / 184 /
+//   177 / 369 / 686; 1 M, 8 M uniform, 67 / 224 / 200 / 341 / 671 -> 61 / 207 / 186 /
+//   346 / 675.
+// - down to 32 entries where the gathered ids are local too: the rows in flight at
+//   once are then closer together, and so is what they gather: grid of 10^6 cells,
+//   b = 128, 128 -> 32 entries: 336 -> 300 us (b = 64: 170 -> 162, b = 10: 74 -> 62,
+//   b = 32: 77 -> 82).  With ids spread evenly there is nothing to bring together,
+//   and the starts of more chunks cost: 500 k entities with 10 triples each, b = 32,
+//   128 -> 32 entries: 114 -> 127 us.
 int32_t entity_chunk(const LayoutHost &layout, int64_t n_entities);
 
 // Returns "" when the triple arrays are valid, else a message; *range_error

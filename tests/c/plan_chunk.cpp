@@ -1,6 +1,6 @@
-// The chunk length of the entity layouts: shorter than the default only where the
-// gathered ids are local and few rows would be split, and never with more
-// partial slots than the default length without packing.  Exit status 0 when
+// The chunk length of the entity layouts: shorter than the default only where few
+// rows would be split, below 128 only where the gathered ids are local too, and
+// never with more partial slots than the default length without packing.  Exit status 0 when
 // every check holds.  Built and run by tests/test_plan_chunk.py.
 #define main plan_sanitized_main
 #include "plan_sanitized.cpp"
@@ -65,6 +65,9 @@ int main() {
   }
   rows_case("even ids, 10 a row", 200'000, 10, 0, 0);
   rows_case("even ids, 80 a row", 30'000, 80, 0, 0);
+  // Above 8.4 M entries (256): halved for rows of up to 16 triples.
+  rows_case("even ids, 10 a row, many", 800'000, 10, 0, 128);
+  rows_case("even ids, 20 a row", 420'000, 20, 0, 0);
   rows_case("local ids, 4 a row", 400'000, 4, 500, 32);
   rows_case("local ids, 5 a row", 400'000, 5, 500, 0);  // longer than an eighth of 32
   rows_case("local ids, 80 a row", 30'000, 80, 500, 0);

@@ -1,5 +1,5 @@
-"""Chunk lengths of the entity layouts (CPU): short chunks only where they bring
-local ids together and split few rows; a forward pass then never needs more
+"""Chunk lengths of the entity layouts (CPU): short chunks only where they split
+few rows, and the shortest only where they bring local ids together; a forward pass then never needs more
 scratch than default chunks without packing, which bounds what
 kb_follow_noalloc's fixed scratch has to hold."""
 import os
