@@ -859,7 +859,8 @@ __device__ __forceinline__ void combine_tasks(const int4 *__restrict__ tasks, in
 }
 
 // A wide combine task: one workgroup adds slots [first, first + n) of up to 32
-// columns.  Its lane groups (of at most 8 lanes, so 32 of them or more) take
+// columns of the launch's slice blockIdx.y (so at most four workgroups per task
+// and slice: the grid's width is a matter of the tasks alone).  Its lane groups (of at most 8 lanes, so 32 of them or more) take
 // every GPB-th slot each, eight loads in flight, and the first one adds the
 // groups' sums in order: a thousand slots in about four rounds of loads, where
 // tasks of 32 slots took two launches more for a hub row.
@@ -871,13 +872,13 @@ __device__ __forceinline__ void combine_wide(const TailArgs &a, int64_t block) {
   constexpr int GPB = kBlock / WL;
   __shared__ double part[GPB][W];
   const int lane = threadIdx.x % WL, grp = threadIdx.x / WL;
-  const int slices = (a.b + W - 1) / W;
-  const int c0 = (int)(block % slices) * W + lane * VEC;
+  constexpr int PARTS = LPT / WL;
+  const int c0 = blockIdx.y * (LPT * VEC) + (int)(block % PARTS) * W + lane * VEC;
   const bool active = c0 < a.b;
   const int c = active ? lane_cols<RAGGED>(c0, a.b).c : 0;
   const int skip = active ? lane_cols<RAGGED>(c0, a.b).skip : 0;
   const size_t bb = (size_t)a.b;
-  const int4 tk = a.tasks[block / slices];  // first, n, dst
+  const int4 tk = a.tasks[block / PARTS];  // first, n, dst
   double acc[VEC];
 #pragma unroll
   for (int v = 0; v < VEC; ++v) acc[v] = 0.0;
@@ -1028,13 +1029,12 @@ __global__ __launch_bounds__(kBlock) void fill_kernel(float *__restrict__ p, int
   }
 }
 
-// The blocks of a combine launch: blocks [0, wide_blocks) of the first slice
-// take the wide tasks (and their slices), the next combine_blocks the others;
-// true for the blocks after them.
+// The blocks of a combine launch: blocks [0, wide_blocks) take the wide tasks, the
+// next combine_blocks the others; true for the blocks after them.
 template <int VEC, int LPT, bool RAGGED>
 __device__ __forceinline__ bool combine_launch(const TailArgs &a) {
   if ((int64_t)blockIdx.x < a.wide_blocks) {
-    if (blockIdx.y == 0) combine_wide<VEC, LPT, RAGGED>(a, blockIdx.x);
+    combine_wide<VEC, LPT, RAGGED>(a, blockIdx.x);
     return false;
   }
   const int64_t block = (int64_t)blockIdx.x - a.wide_blocks;
@@ -1399,8 +1399,7 @@ std::string describe_combine(int32_t b) {
 
 // Blocks of the wide and the other combine tasks of a launch.
 static void combine_grid(TailArgs *a, const ColumnTiling &t) {
-  const int w = std::min(t.lpt, kWideLpt) * t.vec;  // columns of a wide task's workgroup
-  a->wide_blocks = a->n_wide * ((a->b + w - 1) / w);
+  a->wide_blocks = a->n_wide * (t.lpt / std::min(t.lpt, kWideLpt));
   a->combine_blocks =
       a->n_tasks > a->n_wide ? blocks_for(a->n_tasks - a->n_wide, kBlock / t.lpt, 0) : 0;
 }
