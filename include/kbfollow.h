@@ -82,7 +82,8 @@ typedef enum {
  * The three sorted layouts (by object, by subject, by relation) and their
  * work plans are built on the host and uploaded; the host copies are freed.
  * Device memory held: 8 bytes per triple per layout (24 per triple; 36 with
- * weights) plus about 8 bytes per non-empty row per layout.  Building sorts
+ * weights) plus about 8 bytes per non-empty row per layout, and up to an eighth
+ * of that again where chunks end in no-op entries.  Building sorts
  * the triples three ways (radix sorts of one 64-bit key per triple when
  * 2 * bits(N_E - 1) + bits(N_R - 1) <= 64, else chained counting sorts) on
  * up to 16 host threads (the calling thread plus threads it starts and joins
@@ -251,9 +252,10 @@ kb_status kb_follow_backward_residual(const kb_t *kb, int32_t b, const float *X,
  *       then writes that row of Y); otherwise Z must not overlap Y.  Z may
  *       be X or overlap X or R (it is only read).
  * Other arguments, the workspace and the errors as for kb_follow (KB_EINVAL
- * also for a NULL Z or a Z that overlaps Y without being Y).  Raw buffer
- * loads need the added rows to come from X, so with any other Z the
- * forward pass takes the plain-load path (a few percent slower).  The
+ * also for a NULL Z or a Z that overlaps Y without being Y).  X and Z are
+ * read through one raw buffer over both arrays; where the two span 4 GB or
+ * more in memory (so also wherever they are that large together), the forward
+ * pass takes the plain-load path, a few percent slower with the same bits.  The
  * gradient is kb_follow_backward's for X and R and gamma * dY for Z.
  */
 kb_status kb_follow_accumulate(const kb_t *kb, int32_t b, const float *X, const float *R,

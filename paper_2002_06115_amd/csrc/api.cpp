@@ -262,7 +262,12 @@ int lane_cap(const kb_t *kb, int ph_base, int32_t b) {
 // sweep (forward at b = 10: 1780 -> 888 us, b = 8: 926 -> 740, b = 24: 1350 ->
 // 1130, b = 1: 588 -> 508; at b = 32 the sweep would lose, 885 -> 936).  The
 // residual hop's fill also reads a row for each (b = 10: 2020 -> 1352 us, b =
-// 32: 1207 -> 1315, not taken).  The sweep is one more launch.
+// 32: 1207 -> 1315, not taken).  The sweep is one more launch, for which it must
+// gain 6.5 us (2 with res, whose row-by-row fill already costs 2 us more at any
+// size).  That keeps passes of a few microseconds without it although the
+// kernels alone would gain: 75 k entities, 154 k triples, b = 10, forward 9.8 (rows)
+// and 8.8 (sweep), residual 12.9 and 10.2; 300 k, 600 k, 22.7 and 21.6, 35.7 and 31.3;
+// 1 M, 1.5 M, 79 and 61 (taken), 109 and 94 (taken).
 bool prefill_rows(const kb_t *kb, const DevLayout &D, int32_t b, bool res) {
   if (D.n_empty == 0 || D.rows > (int64_t(1) << 33) / b) return false;
   if (kb->prefill >= 0) return kb->prefill > 0;
@@ -274,22 +279,27 @@ bool prefill_rows(const kb_t *kb, const DevLayout &D, int32_t b, bool res) {
   return (double)D.n_empty * row > (double)D.rows * sweep + (res ? 2e6 : 6.5e6);
 }
 
-// Runs one pass: the stream kernel, the first combine level together with
-// the empty rows, the further combine levels.  With Z non-null (one row per
-// output row; A itself for the residual hop, out itself to add in place)
-// every output row j also gets gamma * Z[j].
+// The sweep that a pass over layout D starts with, where prefill_rows takes it
+// (*swept then says so to run_pass).
+kb_status run_sweep(const kb_t *kb, const DevLayout &D, int ph_base, int32_t b, float *out,
+                    const float *Z, float gamma, hipStream_t s, bool *swept) {
+  *swept = Z != out && prefill_rows(kb, D, b, Z != nullptr);
+  if (!*swept) return KB_OK;
+  PhaseScope scope(kb, ph_base + 1, s);
+  scope.counts = false;  // the tail's bracket in run_pass counts for both
+  hipError_t e = launch_fill(out, D.rows * (int64_t)b, Z, gamma, s);
+  return e == hipSuccess ? KB_OK : hip_fail(e, "fill kernel launch");
+}
+
+// Runs one pass after its sweep: the stream kernel, the first combine level
+// together with the empty rows (unless swept), the further combine levels.
+// With Z non-null (one row per output row; A itself for the residual hop, out
+// itself to add in place) every output row j also gets gamma * Z[j].
 kb_status run_pass(const kb_t *kb, const DevLayout &D, int ph_base, const float *A,
                    int64_t A_rows, const float *B, int64_t B_rows, int32_t b, float *out,
-                   void *ws, const float *Z, float gamma, hipStream_t s) {
+                   void *ws, const float *Z, float gamma, bool swept, hipStream_t s) {
   double *slots = static_cast<double *>(ws);
   const float *res = Z;
-  const bool prefill = Z != out && prefill_rows(kb, D, b, Z != nullptr);
-  if (prefill) {
-    PhaseScope scope(kb, ph_base + 1, s);
-    scope.counts = false;  // the tail's bracket below counts for both
-    hipError_t e = launch_fill(out, D.rows * (int64_t)b, res, gamma, s);
-    if (e != hipSuccess) return hip_fail(e, "fill kernel launch");
-  }
   if (D.n > 0) {
     // Timed by the kernel's own timestamps: no event packets between this
     // launch and the next, which would hold back a concurrent pass.
@@ -311,7 +321,7 @@ kb_status run_pass(const kb_t *kb, const DevLayout &D, int ph_base, const float 
     PhaseScope scope(kb, ph_base + 1, s);
     const int64_t n0 = D.level_begin.size() > 1 ? D.level_begin[1] - D.level_begin[0] : 0;
     const int64_t w0 = n0 > 0 ? D.level_wide[0] : 0;
-    TailArgs t{D.ctasks, n0, w0, slots, D.n_slots, D.empty, prefill ? 0 : D.n_empty_pieces, b, out,
+    TailArgs t{D.ctasks, n0, w0, slots, D.n_slots, D.empty, swept ? 0 : D.n_empty_pieces, b, out,
                D.rows, res, gamma, 0, 0};
     hipError_t e = launch_tail(t, s);
     if (e != hipSuccess) return hip_fail(e, "combine and empty-row kernel launch");
@@ -633,8 +643,12 @@ kb_status follow_impl(const kb_t *kb, int32_t b, const float *X, const float *R,
     g_last_error.clear();
     if (!ent_bytes) return KB_OK;
     // By object, runs of equal relation: Y[o] = sum over runs of R[r] (.) sum of X[s].
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    bool swept = false;
+    st = run_sweep(kb, kb->L[BY_OBJ], KB_PH_FWD_STREAM, b, Y, Z, gamma, s, &swept);
+    if (st != KB_OK) return st;
     return run_pass(kb, kb->L[BY_OBJ], KB_PH_FWD_STREAM, X, kb->n_entities, R, kb->n_relations,
-                    b, Y, workspace, Z, gamma, static_cast<hipStream_t>(stream));
+                    b, Y, workspace, Z, gamma, swept, s);
   } catch (...) {
     return fail(KB_EINVAL, "unexpected host error");
   }
@@ -681,6 +695,20 @@ kb_status backward_impl(const kb_t *kb, int32_t b, const float *X, const float *
                          (kb->overlap_backward == 1 || (kb->overlap_backward == -1 && b <= 32));
     std::unique_lock<std::mutex> lock(kb->side_mu, std::defer_lock);
     hipStream_t dr_s = s;
+    // dX's sweep before the fork: beside dR's workgroups, which fill the chip
+    // first, it took long and dX's stream kernel, whose LDS variant's workgroups
+    // wait for a whole CU's share, began late.  Backward, us, after / before the
+    // fork: 3 M entities, 15 M triples, b = 8 / 10 / 24: 425 / 457 / 608 -> 373 /
+    // 431 / 533 (row by row, with a tail that dR's kernel hides: 407 / 538 / 576);
+    // 12.9 M, 43.7 M, 1223 / 1367 / 1848 -> 1182 / 1375 / 1677.  It loses 0.5 to 2
+    // % at b = 9 .. 15 where the output passes 256 MB, 5 % at b = 4 and 5 of one KB
+    // of eight.
+    const float *Z = residual ? dY : nullptr;
+    bool dx_swept = false, dr_swept = false;
+    if (want_dx) {
+      st = run_sweep(kb, kb->L[BY_SUBJ], KB_PH_DX_STREAM, b, dX, Z, gamma, s, &dx_swept);
+      if (st != KB_OK) return st;
+    }
     if (overlap) {
       lock.lock();
       hipError_t e = hipEventRecord(kb->ev_fork, s);
@@ -692,12 +720,14 @@ kb_status backward_impl(const kb_t *kb, int32_t b, const float *X, const float *
       // By subject, runs of equal relation: dX[s] = sum over runs of R[r] (.) sum of dY[o]
       // (+ gamma * dY[s] for the residual hop).
       st = run_pass(kb, kb->L[BY_SUBJ], KB_PH_DX_STREAM, dY, kb->n_entities, R, kb->n_relations,
-                    b, dX, workspace, residual ? dY : nullptr, gamma, s);
+                    b, dX, workspace, Z, gamma, dx_swept, s);
     }
+    if (st == KB_OK && want_dr)
+      st = run_sweep(kb, kb->L[BY_REL], KB_PH_DR_STREAM, b, dR, nullptr, 0.0f, dr_s, &dr_swept);
     if (st == KB_OK && want_dr) {
       // By relation, runs of equal subject: dR[k] = sum over runs of X[s] (.) sum of dY[o].
       st = run_pass(kb, kb->L[BY_REL], KB_PH_DR_STREAM, dY, kb->n_entities, X, kb->n_entities,
-                    b, dR, dr_ws, nullptr, 0.0f, dr_s);
+                    b, dR, dr_ws, nullptr, 0.0f, dr_swept, dr_s);
     }
     if (overlap) {
       // Joined whatever happened above, so the caller's stream never runs

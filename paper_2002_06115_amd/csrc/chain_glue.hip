@@ -20,10 +20,11 @@
 // Long columns (two launches, with the caller's scratch): the rows are cut
 // into ranges, one workgroup per tile and range; the first launch writes each
 // range's partial values, the second combines them (every workgroup for its
-// own columns, the same order everywhere) and writes its range.  Bound by
-// memory then: 43,000 rows of 128 columns (22 MB), L1 normalisation 317 -> 26
-// us, its backward 333 -> 26, cross-entropy 977 -> 45 (with 8 workgroups of 16
-// columns over all rows before).
+// own columns, the same order everywhere) and writes its range.  43,000 rows of
+// 128 columns (22 MB), L1 normalisation 317 -> 26 us, its backward 333 -> 26,
+// cross-entropy 977 -> 45 (with 8 workgroups of 16 columns over all rows before):
+// 1.5 to 1.7 TB/s of the bytes they cannot do without, 4 bytes a lane and four
+// rows deep.
 #include <hip/hip_runtime.h>
 
 #include <cmath>

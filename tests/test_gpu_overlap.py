@@ -62,6 +62,35 @@ def test_overlap_matches_serial_and_oracle(kbf, gamma, monkeypatch):
     assert_close(from_em(outs[True][1]), wdR, "dR")
 
 
+@pytest.mark.parametrize("gamma", [None, 0.5])
+@pytest.mark.parametrize("b", [3, 10, 32])
+def test_overlap_with_sweeps(kbf, b, gamma, monkeypatch):
+    """The sweeps over dX (before the fork) and dR (on the KB's stream) and the rows
+    that the passes write after them, into outputs full of NaN, against the serial
+    passes that write the empty rows one by one."""
+    import torch
+    g = np.random.default_rng(b)
+    n_e, n_r, n_t = 30_000, 500, 60_000  # most subjects and some relations without triples
+    s, o = g.integers(0, n_e // 3, n_t), g.integers(0, n_e, n_t)
+    r = g.integers(0, n_r - 90, n_t)
+    X, R, dY = (torch.from_numpy(g.standard_normal((n, b)).astype(np.float32)).cuda()
+                for n in (n_e, n_r, n_e))
+    outs = {}
+    for mode in ("0", "1"):
+        monkeypatch.setenv("KBFOLLOW_PREFILL", mode)
+        monkeypatch.setenv("KBFOLLOW_OVERLAP_BACKWARD", mode)
+        kb = kbf.KB(s.astype(np.int32), r.astype(np.int32), o.astype(np.int32), n_e, n_r)
+        assert kb.phase_kernels(b)["dx_tail"].startswith("fill_kernel") == (mode == "1")
+        for _ in range(3):
+            dX, dR = torch.full_like(X, np.nan), torch.full_like(R, np.nan)
+            kb.follow_backward(X, R, dY, dX=dX, dR=dR, residual=gamma)
+        torch.cuda.synchronize()
+        outs[mode] = dX, dR
+        kb.close()
+    for a, c in zip(outs["0"], outs["1"]):
+        assert torch.equal(bits(a), bits(c))
+
+
 def test_overlap_graph_replay(kbf, monkeypatch):
     import torch
     w, kb = workload(8)
