@@ -490,9 +490,6 @@ kb_status kb_create(int64_t n_entities, int64_t n_relations, int64_t n_triples,
       // which keeps runs of equal subject, whose X row is read once per run.
       const int32_t n_xcd = std::max(1, std::min(kMaxXcd, env_int("KBFOLLOW_XCD", 8)));
       const int64_t hub_min = std::max(1, env_int("KBFOLLOW_HUB_MIN", 256));
-      auto chunk_of = [&](int k) {
-        return whole_steps(env_int("KBFOLLOW_CHUNK", entity_chunk(H[k], n_entities)));
-      };
       const bool band = env_int("KBFOLLOW_BAND", 1) != 0;
       // dR's lists are classed by subject (the X row read once per run) when
       // the objects are skewed, by the gathered object when they are not
@@ -529,11 +526,13 @@ kb_status kb_create(int64_t n_entities, int64_t n_relations, int64_t n_triples,
       const int32_t chunk_rel = whole_steps(
           env_int("KBFOLLOW_REL_CHUNK", std::min<int32_t>(dr_class_b ? 128 : 64,
                                                           default_chunk(n_triples + n_relations))));
-      const int32_t plen[3] = {chunk_of(BY_OBJ), chunk_of(BY_SUBJ), chunk_rel};
+      int32_t plen[3] = {0, 0, chunk_rel};
       PlanHost P[3];
       std::exception_ptr err[3];
       auto plan = [&](int k) {
         try {
+          if (k != BY_REL)
+            plen[k] = whole_steps(env_int("KBFOLLOW_CHUNK", entity_chunk(H[k], n_entities)));
           PlanOptions po;
           po.chunk = plen[k];
           po.fan_in = fan_in;

@@ -417,16 +417,6 @@ static int64_t compact_ids(std::vector<int32_t> &col, int threads) {
   return ids;
 }
 
-double hub_share(const std::vector<int32_t> &row, int64_t len) {
-  int64_t in_hubs = 0;
-  const int64_t n = (int64_t)row.size();
-  for (int64_t beg = 0, end; beg < n; beg = end) {
-    for (end = beg + 1; end < n && row[end] == row[beg];) ++end;
-    if (end - beg >= len) in_hubs += end - beg;
-  }
-  return n ? (double)in_hubs / (double)n : 0.0;
-}
-
 bool local_ids(const LayoutHost &L) {
   constexpr int64_t kSamples = 4096;
   const int64_t n = (int64_t)L.row.size();
@@ -465,9 +455,18 @@ int32_t default_chunk(int64_t entries) {
 int32_t entity_chunk(const LayoutHost &L, int64_t n_entities) {
   const int64_t entries = (int64_t)L.row.size() + n_entities;
   int32_t c = default_chunk(entries);
+  if (c <= 32 || entries / c >= 98304) return c;
+  // Triples in rows longer than an eighth of 32, 64 and 128 entries.
+  const int64_t n = (int64_t)L.row.size();
+  int64_t longer[3] = {};
+  for (int64_t beg = 0, end; beg < n; beg = end) {
+    for (end = beg + 1; end < n && L.row[end] == L.row[beg];) ++end;
+    for (int k = 0; k < 3; ++k)
+      if (end - beg > (4 << k)) longer[k] += end - beg;
+  }
   // Few chunks yet, and few rows that half of c could split.
   auto halve = [&]() {
-    return c > 32 && entries / c < 98304 && hub_share(L.row, c / 16 + 1) <= 0.125;
+    return c > 32 && entries / c < 98304 && longer[c == 64 ? 0 : c == 128 ? 1 : 2] <= n / 8;
   };
   if (!halve()) return c;
   if (c == 256) c = 128;

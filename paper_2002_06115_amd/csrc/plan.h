@@ -145,9 +145,6 @@ struct PlanHost {
 // ceil(frac * n_ids) most frequent ones: how skewed the id distribution is.
 double top_id_share(const std::vector<int32_t> &col, int64_t n_ids, double frac);
 
-// The share of a sorted layout's triples that lie in rows of at least `len`.
-double hub_share(const std::vector<int32_t> &row, int64_t len);
-
 // Whether the rows of a layout that follow each other gather from places that
 // are near each other (a grid, a band matrix): half of the sampled pairs of
 // neighbouring rows are closer, by the id that their middle triples gather, than
