@@ -47,10 +47,10 @@ struct Span {
 };
 
 template <int TW, int THREADS>
-__device__ __forceinline__ Span span(int64_t r0, int64_t r1, int32_t b, int64_t tile) {
+__device__ __forceinline__ Span span(int64_t r0, int64_t r1, int32_t b, uint32_t tile) {
   Span s;
-  const int64_t col = tile * TW + threadIdx.x % TW;
-  s.col = col < b ? (int)col : b;
+  const uint32_t col = tile * TW + threadIdx.x % TW;  // below 2^31 + 2^8
+  s.col = col < (uint32_t)b ? (int)col : b;
   s.begin = r0 + (int64_t)(threadIdx.x / TW);
   s.end = r1;
   s.step = THREADS / TW;
@@ -281,15 +281,17 @@ __device__ __forceinline__ void apply(const Args &a, const Span &s, const Stats 
 }
 
 // One launch: all rows of TW columns.  Tiles that share cache lines are on one
-// XCD (workgroup w runs on XCD w mod 8; the grid is a multiple of 8): in order,
+// XCD (workgroup w runs on XCD w mod 8; a grid of more than 8 is a multiple of
+// 8): in order,
 // every XCD's L2 fetched every line, which cost wide arrays up to 3.5 times the
 // time (1000 rows of 2048 columns, 4-column tiles, softmax backward 46 -> 12 us).
-constexpr int kXcds = 8;
+constexpr uint32_t kXcds = 8;
 template <int OP, int TW, int THREADS>
 __global__ __launch_bounds__(THREADS) void column_kernel(Args a) {
   __shared__ double lds[3 * (THREADS / 64) * TW];
-  const Span s = span<TW, THREADS>(
-      0, a.n, a.b, (int64_t)(blockIdx.x % kXcds) * (gridDim.x / kXcds) + blockIdx.x / kXcds);
+  const uint32_t share = (gridDim.x + kXcds - 1) / kXcds;
+  const Span s =
+      span<TW, THREADS>(0, a.n, a.b, blockIdx.x % kXcds * share + blockIdx.x / kXcds);
   const Stats r = reduce_combine<OP, TW, THREADS>(reduce_part<OP>(a, s), lds);
   apply<OP>(a, s, r, s.valid && threadIdx.x < TW);
 }
@@ -432,9 +434,9 @@ kbc_status launch(Args a, double *scratch, hipStream_t s) {
     return launched();
   }
   auto go = [&](auto kernel, int tw, int threads) {
-    const int64_t tiles = ((int64_t)a.b + tw - 1) / tw;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)((tiles + kXcds - 1) / kXcds * kXcds)), dim3(threads),
-                       0, s, a);
+    int64_t tiles = ((int64_t)a.b + tw - 1) / tw;
+    if (tiles > kXcds) tiles = (tiles + kXcds - 1) / kXcds * kXcds;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)tiles), dim3(threads), 0, s, a);
   };
   // Narrow tiles give a narrow array more workgroups, wide ones read more of each
   // line.  The five operations together, us, with 4 / 8 / 16 columns (512, 512
