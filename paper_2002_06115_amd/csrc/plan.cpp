@@ -335,12 +335,18 @@ void build_layouts(int64_t n_entities, int64_t n_relations, int64_t n_triples,
               weight, keep_perm);
 }
 
+// Small rows that wait for a chunk with room for them (PlanOptions::pack).
+constexpr size_t kPackWindow = 32;
+
 // Rows [first, first + count) as pieces of at most kEmptyPiece rows.
 static void add_empty(PlanHost &P, int64_t first, int64_t count) {
   P.n_empty_rows += count;
   for (int64_t q = first; q < first + count; q += kEmptyPiece)
     P.empty.push_back({(int32_t)q, (int32_t)std::min<int64_t>(kEmptyPiece, first + count - q)});
 }
+
+// Ids that are dealt to the classes one by one, the heaviest (id_classes).
+constexpr int64_t kHeavyIds = 65536;
 
 // Classes of the ids below n_ids, about equal in the number of triples of `col`
 // with each: the others than the heaviest cut into n_xcd consecutive ranges
@@ -355,7 +361,7 @@ static std::vector<uint8_t> id_classes(const std::vector<int32_t> &col, int64_t 
   std::vector<int32_t> cnt(n_ids, 0);
   for (int32_t a : col) ++cnt[a];
   std::vector<uint8_t> cls(n_ids);
-  const int64_t k_heavy = std::min<int64_t>(n_ids, 65536);
+  const int64_t k_heavy = std::min<int64_t>(n_ids, kHeavyIds);
   // The k_heavy heaviest ids (ties to the smaller id), heaviest first: the
   // count of the k-th one from a selection, then the ids above it and as
   // many of those at it as are needed, in id order.
@@ -417,61 +423,60 @@ static int64_t compact_ids(std::vector<int32_t> &col, int threads) {
   return ids;
 }
 
-bool local_ids(const LayoutHost &L) {
-  constexpr int64_t kSamples = 4096;
-  const int64_t n = (int64_t)L.row.size();
-  if (n == 0) return false;
-  // The middle triple of the row at position p, and the row after it.
-  auto middle = [&](int64_t p, int64_t *next) {
-    const auto r = std::equal_range(L.row.begin(), L.row.end(), L.row[p]);
-    *next = r.second - L.row.begin();
-    return (int64_t)L.col_a[(r.first - L.row.begin()) + (r.second - r.first) / 2];
-  };
-  std::vector<int64_t> near, far;
-  for (int64_t i = 0; i < kSamples; ++i) {
-    int64_t next, other, skip;
-    const int64_t id = middle(i * n / kSamples, &next);
-    if (next >= n) break;
-    other = middle((i + kSamples / 2) % kSamples * n / kSamples, &skip);
-    far.push_back(std::abs(other - id));
-    near.push_back(std::abs(middle(next, &skip) - id));
-  }
-  if (near.size() < kSamples / 2) return false;
-  auto median = [](std::vector<int64_t> &v) {
-    std::nth_element(v.begin(), v.begin() + (std::ptrdiff_t)(v.size() / 2), v.end());
-    return v[v.size() / 2];
-  };
-  // (Neighbours that gather one and the same id are alike, not near.)
-  const int64_t m = median(near);
-  return m > 0 && m <= median(far) / 16;
-}
-
 int32_t default_chunk(int64_t entries) {
   int32_t c = 256;
   while (c > 16 && entries / c < 32768) c /= 2;
   return c;
 }
 
-int32_t entity_chunk(const LayoutHost &L, int64_t n_entities) {
-  const int64_t entries = (int64_t)L.row.size() + n_entities;
-  int32_t c = default_chunk(entries);
-  if (c <= 32 || entries / c >= 98304) return c;
-  // Triples in rows longer than an eighth of 32, 64 and 128 entries.
-  const int64_t n = (int64_t)L.row.size();
-  int64_t longer[3] = {};
-  for (int64_t beg = 0, end; beg < n; beg = end) {
-    for (end = beg + 1; end < n && L.row[end] == L.row[beg];) ++end;
-    for (int k = 0; k < 3; ++k)
-      if (end - beg > (4 << k)) longer[k] += end - beg;
+// The partial sums of `len` rows (triples each) that packing splits over chunks of
+// `chunk` entries: plan_layout's placement on the lengths alone.
+static int64_t packed_partials(const std::vector<int32_t> &len, int32_t chunk) {
+  std::vector<int32_t> wait;
+  size_t next = 0;
+  int64_t partials = 0, room = chunk;
+  while (next < len.size() || !wait.empty()) {
+    while (wait.size() < kPackWindow && next < len.size()) wait.push_back(len[next++] + 1);
+    size_t pick = 0;
+    while (pick < wait.size() && wait[pick] <= chunk && wait[pick] > room) ++pick;
+    if (pick == wait.size()) {
+      if (room <= chunk / 8) {
+        room = chunk;
+        continue;
+      }
+      pick = 0;
+    }
+    int64_t left = wait[pick] - room;  // past this chunk's end
+    if (left > 0) {
+      partials += 1 + (left + chunk - 2) / (chunk - 1);
+      left %= chunk;
+      room = left > 0 ? chunk - left : chunk;
+    } else {
+      room = left < 0 ? -left : chunk;
+    }
+    wait.erase(wait.begin() + (std::ptrdiff_t)pick);
   }
-  // Few chunks yet, and few rows that half of c could split.
-  auto halve = [&]() {
-    return c > 32 && entries / c < 98304 && longer[c == 64 ? 0 : c == 128 ? 1 : 2] <= n / 8;
-  };
-  if (!halve()) return c;
-  if (c == 256) c = 128;
-  if (local_ids(L))
-    while (halve()) c /= 2;
+  return partials;
+}
+
+int32_t entity_chunk(const LayoutHost &L, int64_t n_entities) {
+  constexpr int64_t kSample = 65536;
+  const int64_t n = (int64_t)L.row.size(), entries = n + n_entities;
+  int32_t c = default_chunk(entries);
+  if (n == 0 || c <= 32 || entries / c >= 98304) return c;
+  int64_t rows = 0;
+  for (int64_t l = 0; l < n; ++l) rows += l == 0 || L.row[l] != L.row[l - 1];
+  // Every so many rows' lengths, in their order.
+  const int64_t every = std::max<int64_t>(1, rows / kSample);
+  std::vector<int32_t> len;
+  int64_t q = 0;
+  for (int64_t beg = 0, end; beg < n; beg = end, ++q) {
+    for (end = beg + 1; end < n && L.row[end] == L.row[beg];) ++end;
+    if (q % every == 0) len.push_back((int32_t)(end - beg));
+  }
+  while (c > 32 && entries / c < 98304 && 5 * n <= rows * (c / 2) &&
+         packed_partials(len, c / 2) <= (int64_t)len.size() / 32)
+    c /= 2;
   return c;
 }
 
@@ -559,10 +564,10 @@ PlanHost plan_layout(const LayoutHost &L, const PlanOptions &opt) {
     std::vector<int32_t> idx;
     std::vector<std::pair<uint64_t, int32_t>> kp;
     const int sort_threads = std::max(1, host_threads() / 3);
-    // (Classes of the gathered ids are ranges of them: a_blocks blocks in each.)
+    // (Where classes of the gathered ids are ranges of them, a_blocks to each.)
     const int32_t a_blocks =
         (opt.hub_by_a ? 0 : std::max<int32_t>(0, std::min<int32_t>(opt.a_blocks, 64))) *
-        (opt.class_by_b ? 1 : X);
+        (opt.class_by_b || cls_ids <= kHeavyIds ? 1 : X);
     std::vector<const RowSpan *> small;
     int64_t total = 0;
     for (const RowSpan &r : rows) {
@@ -718,7 +723,6 @@ PlanHost plan_layout(const LayoutHost &L, const PlanOptions &opt) {
       // Segments in order, but one that would cross the chunk's end although
       // a chunk could hold it waits (at most kPackWindow of them) for the next
       // chunk, while later ones that fit are placed.
-      constexpr size_t kPackWindow = 32;
       std::vector<size_t> wait;
       size_t next = 0;
       while (next < segs[x].size() || !wait.empty()) {

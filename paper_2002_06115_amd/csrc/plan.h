@@ -145,33 +145,25 @@ struct PlanHost {
 // ceil(frac * n_ids) most frequent ones: how skewed the id distribution is.
 double top_id_share(const std::vector<int32_t> &col, int64_t n_ids, double frac);
 
-// Whether the rows of a layout that follow each other gather from places that
-// are near each other (a grid, a band matrix): half of the sampled pairs of
-// neighbouring rows are closer, by the id that their middle triples gather, than
-// a sixteenth of what half of the pairs of rows far apart are.
-bool local_ids(const LayoutHost &layout);
-
 // Chunk length of a stream of `entries`: 256, shorter for small ones so that
 // there are at least ~32 K chunks to spread over the GPU (never below 16).
 int32_t default_chunk(int64_t entries);
 
-// Chunk length of the forward or dX layout over n_entities rows: the default, or
-// shorter, for 96 K chunks, where at most an eighth of the triples lie in rows
-// longer than an eighth of the shorter chunk (up to that length a row that does
-// not fit in what is left of a chunk leaves it to no-op markers, so packing splits
-// none).  Longer rows would add partials: 100 k entities with 80 triples each, b =
-// 32, 128 -> 64 entries: 127 -> 148 us, and 67 k -> 220 k slots.
-// - 128 entries instead of 256, forward at b = 1 / 10 / 32 / 64 / 128, us: 2 M
-//   entities, 20 M triples with Zipf subjects, 108 / 270 / 278 / 546 / 994 -> 106 /
-//   259 / 283 / 516 / 1002; 1.5 M, 14 M, 86 / 186 / 188 / 394 / 724 -> 81 / 184 /
-//   177 / 369 / 686; 1 M, 8 M uniform, 67 / 224 / 200 / 341 / 671 -> 61 / 207 / 186 /
-//   346 / 675.
-// - down to 32 entries where the gathered ids are local too: the rows in flight at
-//   once are then closer together, and so is what they gather: grid of 10^6 cells,
-//   b = 128, 128 -> 32 entries: 336 -> 300 us (b = 64: 170 -> 162, b = 10: 74 -> 62,
-//   b = 32: 77 -> 82).  With ids spread evenly there is nothing to bring together,
-//   and the starts of more chunks cost: 500 k entities with 10 triples each, b = 32,
-//   128 -> 32 entries: 114 -> 127 us.
+// Chunk length of the forward or dX layout over n_entities rows: the default,
+// halved (down to 32) while there are fewer than 96 K chunks, the shorter chunk
+// holds five average rows or more and packing splits few (on a sample of row
+// lengths at most a partial sum per 32 rows).  More chunks spread better, and the
+// rows in flight at once are closer together, as is what they gather in a KB with
+// local ids; but their starts and the partials of longer rows cost.  Forward, us,
+// with 256 / 128 / 64 / 32 entries:
+//   2 M entities, 20 M triples, Zipf subjects, b = 10: 270 / 259, b = 64: 546 / 516;
+//   832 k, 3.6 M, b = 8: - / 101 / 87 / 80, b = 32: - / 133 / 114 / 107, b = 128: - /
+//   381 / 370 / 372;
+//   a grid of 10^6 cells, b = 10: - / 74 / 67 / 62, b = 128: - / 336 / 329 / 300;
+//   500 k, 10 triples a row, b = 32: 113 / 114 / 118 / 127;
+//   300 k, 30 a row, b = 32: 175 / 200 / 191 / 217;
+//   100 k, 80 a row, b = 32: 140 / 127 / 148 / 161 (67 k partial slots at 128, 220 k at
+//   64).
 int32_t entity_chunk(const LayoutHost &layout, int64_t n_entities);
 
 // Returns "" when the triple arrays are valid, else a message; *range_error

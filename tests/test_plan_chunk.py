@@ -1,6 +1,6 @@
-"""Chunk lengths of the entity layouts (CPU): short chunks only where they split
-few rows, and the shortest only where they bring local ids together; a forward pass then never needs more
-scratch than default chunks without packing, which bounds what
+"""Chunk lengths of the entity layouts (CPU): shorter than the default only where a
+chunk holds several rows and packing splits few of them; a forward pass then never
+needs more scratch than default chunks without packing, which bounds what
 kb_follow_noalloc's fixed scratch has to hold."""
 import os
 import shutil
