@@ -860,7 +860,8 @@ __device__ __forceinline__ void combine_tasks(const int4 *__restrict__ tasks, in
 
 // A wide combine task: one workgroup adds slots [first, first + n) of up to 32
 // columns of the launch's slice blockIdx.y (so at most four workgroups per task
-// and slice: the grid's width is a matter of the tasks alone).  Its lane groups (of at most 8 lanes, so 32 of them or more) take
+// and slice: the grid's width is a matter of the tasks alone; all tasks' first
+// parts come first, so that each part is spread over the XCDs).  Its lane groups (of at most 8 lanes, so 32 of them or more) take
 // every GPB-th slot each, eight loads in flight, and the first one adds the
 // groups' sums in order: a thousand slots in about four rounds of loads, where
 // tasks of 32 slots took two launches more for a hub row.
@@ -872,13 +873,15 @@ __device__ __forceinline__ void combine_wide(const TailArgs &a, int64_t block) {
   constexpr int GPB = kBlock / WL;
   __shared__ double part[GPB][W];
   const int lane = threadIdx.x % WL, grp = threadIdx.x / WL;
-  constexpr int PARTS = LPT / WL;
-  const int c0 = blockIdx.y * (LPT * VEC) + (int)(block % PARTS) * W + lane * VEC;
+  const uint32_t blk = (uint32_t)block, n_wide = (uint32_t)a.n_wide;
+  const int part0 = blockIdx.y * (LPT * VEC) + (int)(blk / n_wide) * W;
+  if (part0 >= a.b) return;  // the whole workgroup: the last slice's columns end before
+  const int c0 = part0 + lane * VEC;
   const bool active = c0 < a.b;
   const int c = active ? lane_cols<RAGGED>(c0, a.b).c : 0;
   const int skip = active ? lane_cols<RAGGED>(c0, a.b).skip : 0;
   const size_t bb = (size_t)a.b;
-  const int4 tk = a.tasks[block / PARTS];  // first, n, dst
+  const int4 tk = a.tasks[blk % n_wide];  // first, n, dst
   double acc[VEC];
 #pragma unroll
   for (int v = 0; v < VEC; ++v) acc[v] = 0.0;
