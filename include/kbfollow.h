@@ -96,7 +96,7 @@ typedef enum {
  *   KBFOLLOW_CHUNK, KBFOLLOW_REL_CHUNK  entries per chunk of the entity and
  *                                       relation layouts (default 256 and
  *                                       128, less for small KBs and for those
- *                                       with local ids; rounded up to 8);
+ *                                       with short rows; rounded up to 8);
  *   KBFOLLOW_FAN_IN                     partials per combine task (32; set, it
  *                                       turns wide tasks off);
  *   KBFOLLOW_WIDE                       partials per wide combine task, a
